@@ -782,10 +782,11 @@ int time_mod_chain(hipStream_t st, const ardit_dims* d, int B, const float* t_ho
   auto B16 = [](const void* q) { return static_cast<const bf16_t*>(q); };
   ARDIT_HIP(launch_time_sinusoid(st, t_host, B, s), "time sinusoid");
   ARDIT_HIP(launch_linear_small(st, s, B, ARDIT_TIME_FREQ_DIM, B16(tw->w_t1), B16(tw->b_t1), D,
-                                e1, false), "time mlp 1");
+                                e1, true),
+            "time mlp 1");
   ARDIT_HIP(launch_linear_small(st, e1, B, D, B16(tw->w_t2), B16(tw->b_t2), D, e2, true),
             "time mlp 2");
-  ARDIT_HIP(launch_linear_small(st, e2, B, D, B16(tw->w_m), B16(tw->b_m), 6 * D, mod_out, true),
+  ARDIT_HIP(launch_linear_small(st, e2, B, D, B16(tw->w_m), B16(tw->b_m), 6 * D, mod_out, false),
             "time modulation");
   return ARDIT_OK;
 }

@@ -199,9 +199,10 @@ hipError_t launch_ctx_k_layout(hipStream_t st, const bf16_t* src, int N, int D, 
                                const bf16_t* gain, float eps, bf16_t* dst,
                                const RowStreams& rs);
 
-// y[b][o] = act_out(sum_k act_in(x[b][k]) W[o][k] + bias[o]); x, y fp32; W, bias bf16.
+// y[b][o] = act(sum_k x[b][k] W[o][k] + bias[o]), act SiLU or none; x, y fp32;
+// W, bias bf16; K % 8 == 0, 16-byte aligned rows.
 hipError_t launch_linear_small(hipStream_t st, const float* x, int B, int K, const bf16_t* W,
-                               const bf16_t* bias, int O, float* y, bool silu_in);
+                               const bf16_t* bias, int O, float* y, bool silu_out);
 hipError_t launch_time_sinusoid(hipStream_t st, const float* t_host, int B, float* s_out);
 
 // ------------------------------------------------------- chunk sampler

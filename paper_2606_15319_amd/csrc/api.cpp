@@ -937,19 +937,17 @@ int ardit_ctx_kv(hipStream_t stream, const ardit_dims* dims, const ardit_batch* 
   bf16_t* cv = at<bf16_t>(ws, L.cv);
   const RowStreams rs = ctx_streams(batch);
   auto B16 = [](const void* q) { return static_cast<const bf16_t*>(q); };
-  GemmEpiArgs e;
-  e.bias = B16(w->b_ck);
-  ARDIT_HIP(launch_gemm(stream, kEpiBias, B16(ctx), D, B16(w->w_ck), D, ck, D, Nc, D, D, e),
-            "ctx k gemm");
+  bool v_done = false;
+  ARDIT_HIP(launch_ctx_gemms(stream, B16(ctx), Nc, D, B16(w->w_ck), B16(w->b_ck), ck, B16(w->w_cv),
+                             B16(w->b_cv), cv, static_cast<bf16_t*>(ctx_v), rs, &v_done),
+            "ctx k / v gemm");
   ARDIT_HIP(launch_ctx_k_layout(stream, ck, Nc, D, dims->n_heads, dims->head_dim, B16(w->g_ck),
                                 dims->eps, static_cast<bf16_t*>(ctx_k), rs),
             "ctx k layout");
-  e.bias = B16(w->b_cv);
-  ARDIT_HIP(launch_gemm(stream, kEpiBias, B16(ctx), D, B16(w->w_cv), D, cv, D, Nc, D, D, e),
-            "ctx v gemm");
-  ARDIT_HIP(launch_v_transpose(stream, cv, D, 0, Nc, D, dims->n_heads, dims->head_dim,
-                               static_cast<bf16_t*>(ctx_v), false, 0, nullptr, 0, 0, rs),
-            "ctx v layout");
+  if (!v_done)
+    ARDIT_HIP(launch_v_transpose(stream, cv, D, 0, Nc, D, dims->n_heads, dims->head_dim,
+                                 static_cast<bf16_t*>(ctx_v), false, 0, nullptr, 0, 0, rs),
+              "ctx v layout");
   return ARDIT_OK;
 } catch (...) {
   return host_failure();

@@ -115,13 +115,22 @@ __device__ __forceinline__ void store4(float* p, const float* y) {
   *reinterpret_cast<float4*>(p) = make_float4(y[0], y[1], y[2], y[3]);
 }
 
-// ResT / OutT: element type of the residual input and of C (bf16 or fp32)
-template <int BM_, int EPI, typename ResT, typename OutT>
+// Second product of a launch: same A and shape, its own weights, bias and result.
+struct GemmSecond {
+  const bf16_t* W = nullptr;
+  const bf16_t* bias = nullptr;
+  bf16_t* C = nullptr;
+};
+
+// ResT / OutT: element type of the residual input and of C (bf16 or fp32).
+// DUAL: column tiles past the first product's belong to the second.
+template <int BM_, int EPI, typename ResT, typename OutT, bool DUAL>
 __global__ __launch_bounds__(NT, 1) void gemm_kernel(const bf16_t* __restrict__ A, int lda,
                                                      const bf16_t* __restrict__ W, int ldw,
                                                      OutT* __restrict__ C, int ldc, int M,
                                                      int N, int K, const GemmEpiArgs ep,
-                                                     int tiles_m, int tiles_n, int per_xcd) {
+                                                     int tiles_m, int tiles_n, int per_xcd,
+                                                     const GemmSecond sec) {
   using G = Cfg<BM_>;
   constexpr int BM = G::BM, STAGES = G::STAGES, WM = G::WM, MB = G::MB;
   constexpr int A_BYTES = G::A_BYTES, STAGE_BYTES = G::STAGE_BYTES, A_INS = G::A_INS;
@@ -135,7 +144,16 @@ __global__ __launch_bounds__(NT, 1) void gemm_kernel(const bf16_t* __restrict__ 
   const int g0 = (L / group) * GROUP_M;
   const int gm = min(tiles_m - g0, GROUP_M);
   const int tm = g0 + (L % group) % gm;
-  const int tn = (L % group) / gm;
+  int tn = (L % group) / gm;
+  const bf16_t* bias_p = ep.bias;
+  if constexpr (DUAL) {   // tiles_n counts both products' column tiles
+    if (tn >= tiles_n / 2) {
+      tn -= tiles_n / 2;
+      W = sec.W;
+      bias_p = sec.bias;
+      C = sec.C;
+    }
+  }
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, g = lane >> 4;
@@ -305,7 +323,7 @@ __global__ __launch_bounds__(NT, 1) void gemm_kernel(const bf16_t* __restrict__ 
   float bias[NB][4];
   if (cols_in) {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) load4(ep.bias + tn * BN + WN * wn + 16 * nb + 4 * g, bias[nb]);
+    for (int nb = 0; nb < NB; ++nb) load4(bias_p + tn * BN + WN * wn + 16 * nb + 4 * g, bias[nb]);
   }
 #pragma unroll
   for (int pass = 0; pass < NPASS; ++pass) {
@@ -357,6 +375,187 @@ __global__ __launch_bounds__(NT, 1) void gemm_kernel(const bf16_t* __restrict__ 
   }
 }
 
+// ------------------------------------------------------------ small products
+// Products of a few hundred rows leave most CUs without a 128 x 256 tile and
+// run at the latency of one tile's K loop, about 0.9 us a step with two steps
+// in flight (text keys and values of 589 tokens, 1536 wide: 50 us in four
+// launches, now 18 us in two; the tiny block, 192 rows of 256: 101 -> 64 us).  Here tiles are small (64 x 128 on eight waves, or 32 x 64 on
+// four, so more CUs take part) and S - 1 steps are in flight through a ring of
+// S LDS stages: at K = 256 a tile's whole operands are requested at once.  One
+// barrier per step: it publishes stage kt and closes the reads of stage kt-1,
+// into which step kt+S-1 is then requested.  Each output element goes through
+// the same MFMA sequence as in gemm_kernel, so C does not depend on which of
+// the kernels computes it.  The epilogue's operands are loaded before the K
+// loop and the results stored from registers (4 columns a lane; the outputs
+// are small).
+//
+// Up to two products of one A (text keys and values) share a launch: the
+// workgroups past the first product's take W2 / bias2.  The second's result
+// may go transposed per head ([H][hd][len] per stream, vt), where 16 lanes
+// hold 16 consecutive tokens of a dim.
+struct SmallDual {
+  const bf16_t* W2 = nullptr;      // second product (null: none), same shape and A
+  const bf16_t* bias2 = nullptr;
+  bf16_t* C2 = nullptr;            // transposed per head and stream
+  RowStreams rs;                   // streams of the rows (len, row_begin)
+};
+
+template <int WM_, int WN_, int MB, int NB, int S, int EPI, typename ResT, typename OutT, bool DUAL>
+__global__ __launch_bounds__(64 * WM_ * WN_, 1) void gemm_small_kernel(
+    const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int ldw,
+    OutT* __restrict__ C, int ldc, int M, int N, int K, const GemmEpiArgs ep, int tiles_m,
+    int tiles_n, const SmallDual du) {
+  constexpr int NW = WM_ * WN_, BM = 16 * MB * WM_, BNS = 16 * NB * WN_;
+  constexpr int AB = BM * ROW_BYTES, WB = BNS * ROW_BYTES, STAGE = AB + WB;
+  constexpr int A_INS = AB / 1024 / NW, WI = WB / 1024 / NW, INS = A_INS + WI;
+  static_assert(A_INS * NW * 1024 == AB && WI * NW * 1024 == WB, "whole 1 KB loads per wave");
+  static_assert(S * STAGE <= 160 * 1024 && S >= 3 && S <= 6, "LDS");
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[S * STAGE];
+  // XCD-aware order: each XCD takes a run of column tiles with all their row
+  // tiles, so a W tile is fetched by one XCD only
+  const int total = (DUAL ? 2 : 1) * tiles_m * tiles_n;
+  const int per_xcd = (total + kNumXcd - 1) / kNumXcd;
+  int p = static_cast<int>(blockIdx.x % kNumXcd) * per_xcd + static_cast<int>(blockIdx.x / kNumXcd);
+  if (p >= total) return;
+  const bool second = DUAL && p >= tiles_m * tiles_n;
+  if (second) p -= tiles_m * tiles_n;
+  const int tm = p % tiles_m, tn = p / tiles_m;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, g = lane >> 4;
+  const int wm = wave / WN_, wn = wave % WN_;
+  const char* a_base = uniform_ptr(A + static_cast<size_t>(tm) * BM * lda);
+  const char* w_base = uniform_ptr((second ? du.W2 : W) + static_cast<size_t>(tn) * BNS * ldw);
+  uint32_t a_off[A_INS], w_off[WI];
+#pragma unroll
+  for (int j = 0; j < A_INS; ++j) {
+    const int r = 8 * (wave * A_INS + j) + (lane >> 3);
+    a_off[j] = static_cast<uint32_t>((min(tm * BM + r, M - 1) - tm * BM) * lda * 2 +
+                                     ((lane & 7) ^ swz(r)) * 16);
+  }
+#pragma unroll
+  for (int j = 0; j < WI; ++j) {   // (N is a multiple of the tile width)
+    const int r = 8 * (wave * WI + j) + (lane >> 3);
+    w_off[j] = static_cast<uint32_t>(r * ldw * 2 + ((lane & 7) ^ swz(r)) * 16);
+  }
+  const uint32_t wave_s = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(wave));
+  const uint32_t smem_s = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(
+      reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const char*)smem))));
+  const uint32_t lds_a = smem_s + wave_s * (A_INS * 1024u);
+  const uint32_t lds_w = smem_s + AB + wave_s * (WI * 1024u);
+  auto issue = [&](int kt, int slot) {
+    const uint32_t so = static_cast<uint32_t>(slot * STAGE);
+    const int koff = kt * ROW_BYTES;
+#pragma unroll
+    for (int j = 0; j < A_INS; ++j) lds_dma16(a_base + koff, a_off[j], lds_a + so + 1024u * j);
+#pragma unroll
+    for (int j = 0; j < WI; ++j) lds_dma16(w_base + koff, w_off[j], lds_w + so + 1024u * j);
+  };
+
+  // epilogue operands, requested first: lane owns row m of block mb, columns n .. n + 3 of nb
+  constexpr bool HAS_RES = EPI == kEpiBiasGateRes || EPI == kEpiBiasRes;
+  const int m0 = tm * BM + 16 * MB * wm + l16, n0 = tn * BNS + 16 * NB * wn + 4 * g;
+  const bf16_t* bias = second ? du.bias2 : ep.bias;
+  float bi[NB][4], res[MB][NB][4], gm[MB][NB][4], gt[NB][4];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    load4(bias + n0 + 16 * nb, bi[nb]);
+    if (EPI == kEpiBiasGateRes) load4(ep.mod_table + static_cast<size_t>(ep.gate_row) * ep.dim + n0 + 16 * nb, gt[nb]);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      const int m = min(m0 + 16 * mb, M - 1);
+      if (HAS_RES)
+        load4(static_cast<const ResT*>(ep.res) + static_cast<size_t>(m) * ep.ldr + n0 + 16 * nb, res[mb][nb]);
+      if (EPI == kEpiBiasGateRes)
+        load4(ep.mod + (static_cast<size_t>(m / ep.rows_per_stream) * 6 + ep.gate_row) * ep.dim + n0 + 16 * nb,
+              gm[mb][nb]);
+    }
+  }
+  // the vector-memory waits below count these loads too (they are older than
+  // every stage's), so they are done whenever the first stage is
+
+  f32x4 acc[MB][NB];
+#pragma unroll
+  for (int a = 0; a < MB; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.f;
+  const int nk = K / BK;
+#pragma unroll
+  for (int i = 0; i < S - 1; ++i)
+    if (i < nk) issue(i, i);
+  int slot = 0;
+  for (int kt = 0; kt < nk; ++kt) {
+    // stage kt has landed once at most the later requested steps are in flight
+    const int rem = min(S - 2, nk - 1 - kt);
+    if (rem >= 4) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * INS));
+    else if (rem == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * INS));
+    else if (rem == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * INS));
+    else if (rem == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(INS));
+    else asm volatile("s_waitcnt vmcnt(0)");
+    __syncthreads();
+    if (kt + S - 1 < nk) issue(kt + S - 1, slot == 0 ? S - 1 : slot - 1);
+    const bf16_t* cA = reinterpret_cast<const bf16_t*>(smem + slot * STAGE);
+    const bf16_t* cW = reinterpret_cast<const bf16_t*>(smem + slot * STAGE + AB);
+    bf16x8 fa[2][MB], fw[2][NB];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const int r = 16 * (NB * wn + nb) + l16;
+        fw[kk][nb] = *reinterpret_cast<const bf16x8*>(&cW[r * BK + 8 * ((4 * kk + g) ^ swz(r))]);
+      }
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        const int r = 16 * (MB * wm + mb) + l16;
+        fa[kk][mb] = *reinterpret_cast<const bf16x8*>(&cA[r * BK + 8 * ((4 * kk + g) ^ swz(r))]);
+      }
+    }
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+          acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[kk][nb], fa[kk][mb], acc[mb][nb], 0, 0, 0);
+    slot = slot == S - 1 ? 0 : slot + 1;
+  }
+
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const int m = m0 + 16 * mb;
+    if (m >= M) continue;
+    size_t vt = 0;   // transposed output: element of (head 0, dim 0, this token)
+    int len = 0;
+    if (second) {
+      int b = 0;
+      for (int i = 1; i < du.rs.n; ++i)
+        if (m >= du.rs.s[i].row_begin) b = i;
+      len = du.rs.s[b].len;
+      vt = static_cast<size_t>(du.rs.s[b].row_begin) * N + (m - du.rs.s[b].row_begin);
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const int n = n0 + 16 * nb;
+      float y[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        y[e] = acc[mb][nb][e] + bi[nb][e];
+        if (EPI == kEpiBiasGelu) y[e] = gelu_tanh(y[e]);
+        if (EPI == kEpiBiasGateRes) y[e] = res[mb][nb][e] + (gm[mb][nb][e] + gt[nb][e]) * y[e];
+        if (EPI == kEpiBiasRes) y[e] = res[mb][nb][e] + y[e];
+      }
+      if (second) {   // (column n = head n / hd, dim n % hd: row n of the stream's [H hd][len])
+#pragma unroll
+        for (int e = 0; e < 4; ++e) du.C2[vt + static_cast<size_t>(n + e) * len] = f2bf(y[e]);
+      } else {
+        store4(C + static_cast<size_t>(m) * ldc + n, y);
+      }
+    }
+  }
+}
+
 }  // namespace
 
 // Tile height for an M x N product.  Both heights give bit-identical C (the
@@ -377,18 +576,89 @@ static void launch_t(hipStream_t st, const bf16_t* A, int lda, const bf16_t* W, 
   const int tiles_m = (M + BM_ - 1) / BM_, tiles_n = (N + BN - 1) / BN;
   const int total = tiles_m * tiles_n;
   const int per_xcd = (total + kNumXcd - 1) / kNumXcd;
-  hipLaunchKernelGGL((gemm_kernel<BM_, EPI, ResT, OutT>), dim3(per_xcd * kNumXcd), dim3(NT), 0, st,
-                     A, lda, W, ldw, static_cast<OutT*>(C), ldc, M, N, K, ep, tiles_m, tiles_n,
-                     per_xcd);
+  hipLaunchKernelGGL((gemm_kernel<BM_, EPI, ResT, OutT, false>), dim3(per_xcd * kNumXcd), dim3(NT), 0,
+                     st, A, lda, W, ldw, static_cast<OutT*>(C), ldc, M, N, K, ep, tiles_m, tiles_n,
+                     per_xcd, GemmSecond{});
+}
+
+// Which small tile, if any (0: the large tiles); N counts both products' columns
+// when two share a launch.  32 x 64 tiles leave room for two workgroups on a CU,
+// 64 x 128 for one, and each is taken while its workgroups fit one round of the
+// chip: past that a second round costs more than the larger tile's lower share
+// of CUs.  Text keys and values of 1536-wide tokens (two products, us): 64
+// tokens 12 / 16 / 27 on 32-row / 64-row / 128-row tiles, 192: 14 / 17 / 28,
+// 512: 21 / 17 / 29, 1560: 48 / 40 / 33; 5120-wide: 64 tokens 37 / 40 / 66,
+// 192: 58 / 42 / 69, 512: 132 / 99 / 71.
+static int small_tile(int M, int N) {
+  if (static_cast<long>((M + 31) / 32) * (N / 64) <= 512) return 32;
+  return static_cast<long>((M + 63) / 64) * (N / 128) <= 256 ? 64 : 0;
+}
+
+template <int WM_, int WN_, int MB, int NB, int EPI, typename ResT, typename OutT, bool DUAL>
+static void launch_small_t(hipStream_t st, const bf16_t* A, int lda, const bf16_t* W, int ldw, void* C,
+                           int ldc, int M, int N, int K, const GemmEpiArgs& ep, const SmallDual& du) {
+  const int tm = (M + 16 * MB * WM_ - 1) / (16 * MB * WM_), tn = N / (16 * NB * WN_);
+  const int wgs = ((DUAL ? 2 : 1) * tm * tn + kNumXcd - 1) / kNumXcd * kNumXcd;
+  hipLaunchKernelGGL((gemm_small_kernel<WM_, WN_, MB, NB, 6, EPI, ResT, OutT, DUAL>), dim3(wgs),
+                     dim3(64 * WM_ * WN_), 0, st, A, lda, W, ldw, static_cast<OutT*>(C), ldc, M, N, K, ep, tm,
+                     tn, du);
+}
+template <int EPI, typename ResT, typename OutT>
+static void launch_small(int tile, hipStream_t st, const bf16_t* A, int lda, const bf16_t* W, int ldw,
+                         void* C, int ldc, int M, int N, int K, const GemmEpiArgs& ep) {
+  if (tile == 32)
+    launch_small_t<2, 2, 1, 2, EPI, ResT, OutT, false>(st, A, lda, W, ldw, C, ldc, M, N, K, ep, SmallDual{});
+  else
+    launch_small_t<2, 4, 2, 2, EPI, ResT, OutT, false>(st, A, lda, W, ldw, C, ldc, M, N, K, ep, SmallDual{});
 }
 
 template <int EPI, typename ResT, typename OutT>
 static void launch_bm(hipStream_t st, const bf16_t* A, int lda, const bf16_t* W, int ldw, void* C,
                       int ldc, int M, int N, int K, const GemmEpiArgs& ep) {
-  if (choose_bm(M, N) == 192)
+  if (const int tile = small_tile(M, N))
+    launch_small<EPI, ResT, OutT>(tile, st, A, lda, W, ldw, C, ldc, M, N, K, ep);
+  else if (choose_bm(M, N) == 192)
     launch_t<192, EPI, ResT, OutT>(st, A, lda, W, ldw, C, ldc, M, N, K, ep);
   else
     launch_t<128, EPI, ResT, OutT>(st, A, lda, W, ldw, C, ldc, M, N, K, ep);
+}
+
+template <int BM_>
+static void launch_dual_t(hipStream_t st, const bf16_t* A, int lda, const bf16_t* W, int ldw, bf16_t* C, int ldc,
+                          int M, int N, int K, const GemmEpiArgs& ep, const GemmSecond& sec) {
+  const int tiles_m = (M + BM_ - 1) / BM_, tiles_n = 2 * ((N + BN - 1) / BN);
+  const int per_xcd = (tiles_m * tiles_n + kNumXcd - 1) / kNumXcd;
+  hipLaunchKernelGGL((gemm_kernel<BM_, kEpiBias, bf16_t, bf16_t, true>), dim3(per_xcd * kNumXcd), dim3(NT), 0,
+                     st, A, lda, W, ldw, C, ldc, M, N, K, ep, tiles_m, tiles_n, per_xcd, sec);
+}
+
+hipError_t launch_ctx_gemms(hipStream_t st, const bf16_t* ctx, int M, int D, const bf16_t* Wk,
+                            const bf16_t* bk, bf16_t* ck, const bf16_t* Wv, const bf16_t* bv, bf16_t* cv,
+                            bf16_t* ctx_v, const RowStreams& rs, bool* v_done) {
+  *v_done = false;
+  if (M == 0) return hipSuccess;
+  if (D % 128 != 0) return hipErrorInvalidValue;
+  GemmEpiArgs e;
+  e.bias = bk;
+  // the tile rule of small_tile on the workgroups of both products
+  const int tile = small_tile(M, 2 * D);
+  if (tile) {
+    SmallDual du{};
+    du.W2 = Wv;
+    du.bias2 = bv;
+    du.C2 = ctx_v;
+    du.rs = rs;
+    if (tile == 32)
+      launch_small_t<2, 2, 1, 2, kEpiBias, bf16_t, bf16_t, true>(st, ctx, D, Wk, D, ck, D, M, D, D, e, du);
+    else
+      launch_small_t<2, 4, 2, 2, kEpiBias, bf16_t, bf16_t, true>(st, ctx, D, Wk, D, ck, D, M, D, D, e, du);
+    *v_done = true;
+  } else {
+    const GemmSecond sec{Wv, bv, cv};
+    if (choose_bm(M, 2 * D) == 192) launch_dual_t<192>(st, ctx, D, Wk, D, ck, D, M, D, D, e, sec);
+    else launch_dual_t<128>(st, ctx, D, Wk, D, ck, D, M, D, D, e, sec);
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_gemm(hipStream_t st, int epi, const bf16_t* A, int lda, const bf16_t* W,

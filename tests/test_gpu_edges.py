@@ -41,3 +41,60 @@ def test_time_mod_rows_and_stream_groups(A, dim, n):
         # random walk of about sqrt(K) 2^-24 of its RMS, 3.2e-6; three of them
         # and a factor of two for the largest of 17k values: 2e-5 of the RMS
         assert np.max(np.abs(got[i] - ref)) <= 2e-5 * np.sqrt(np.mean(ref ** 2)), (dim, n, i)
+
+
+def _ctx_case(A, dim, lens, seed):
+    import torch
+    from harness import upload_block_weights
+    from paper_2606_15319_amd.layout import ctx_from_device_layout
+    from workloads import normal_bf16
+    from workloads.gen import draw_block_weights
+    sh = BlockShape(dim=dim, n_heads=dim // 128, head_dim=128, ffn_dim=128, frames=1, lat_h=8, lat_w=8)
+    w = draw_block_weights(make_rng(seed), sh)
+    rng = make_rng(seed + 1)
+    ctx = [normal_bf16(rng, (n, dim)) for n in lens]
+    dims, batch = A.dims_from_shape(sh), A.Batch(ctx_lens=lens)
+    ck = torch.full((sum(lens) * dim,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    cv = torch.full_like(ck, float("nan"))
+    n = A.ardit_workspace_size(dims, batch)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    A.ardit_ctx_kv(None, dims, batch, dev_bf16(np.concatenate(ctx)), A.block_weights(upload_block_weights(w)),
+                   ck, cv, ws, n)
+    _sync()
+    kf, vf, off, out = host_f32(ck), host_f32(cv), 0, []
+    for b, m in enumerate(lens):
+        sl = slice(off * dim, (off + m) * dim)
+        out.append((*ctx_from_device_layout(kf[sl], vf[sl], m, sh.n_heads, 128), *O.context_kv(ctx[b], w, sh.eps)))
+        off += m
+    return out
+
+
+@pytest.mark.parametrize("dim,lens", [
+    (128, [1]),             # one row, two K steps: fewer than the stages in flight
+    (256, [31, 33, 1]),     # 32-row tiles with a ragged end, streams meeting inside a tile
+    (384, [512, 77]),       # six K steps (the ring wraps once), the last row tile half full
+    (1536, [512, 77]),      # 64-row tiles
+    (1536, [700, 500]),     # the large tiles, both products in one launch, values transposed after
+])
+def test_ctx_kv_tiles(A, dim, lens):
+    from harness import parity
+    for b, (k, v, kr, vr) in enumerate(_ctx_case(A, dim, lens, 410)):
+        parity(k, kr, f"k {dim} {b}", quantum=kr)
+        parity(v, vr, f"v {dim} {b}", quantum=vr)
+
+
+@pytest.mark.parametrize("dim,heads,lat_h,lat_w", [(1024, 8, 26, 40), (256, 4, 7, 24)])
+def test_block_small_products(A, dim, heads, lat_h, lat_w):
+    """The residual epilogues of the small tiles: 1040 rows of 1024 (64-row tiles
+    of the D x D products) and 168 rows of 256 (32-row tiles, a ragged end)."""
+    import dataclasses
+    from harness import BlockRun, parity
+    from workloads import WORKLOADS
+    sh = BlockShape(dim=dim, n_heads=heads, head_dim=dim // heads, ffn_dim=512, frames=1, lat_h=lat_h,
+                    lat_w=lat_w)
+    wl = dataclasses.replace(WORKLOADS["tiny"], shape=sh, cache_chunks=(1,), frame_pos0=(1,), ctx_len=40)
+    run = BlockRun(wl, A, shuffle_pages_seed=3)
+    run.run()
+    _sync()
+    ref = run.reference(0)
+    parity(host_f32(run.out), ref["out"], f"block {dim}")

@@ -17,6 +17,20 @@ namespace ardit {
 constexpr int kMaxChunksPerLane = 16;  // 16 * 8 * 64 = 8192 elements per row
 
 // ------------------------------------------------------------------ norms
+// 16 bytes of a result that this kernel does not read again, written past the
+// L2: a kernel's dirty L2 lines are flushed when it ends, which for these
+// streaming kernels costs more than the later reads gain.  At 4680 rows of 1536
+// the bf16-input adaLN takes 11.0 us for 12.0 and at 37440 rows 48 for 49 (the
+// norms that read fp32 rows gain 1 us at 4680 rows and lose 3 at 37440, so they
+// store normally).
+__device__ __forceinline__ void store_stream(uint4* p, const uint4& v) {
+  __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), reinterpret_cast<u32x4*>(p));
+}
+template <typename T>
+__device__ __forceinline__ void store_row(uint4* p, const uint4& v) {
+  if constexpr (sizeof(T) == 2) store_stream(p, v);
+  else *p = v;
+}
 // 8 consecutive elements of a bf16 or fp32 row as fp32
 __device__ __forceinline__ void load8(const bf16_t* p, float* f) {
   unpack8(*reinterpret_cast<const uint4*>(p), f);
@@ -112,7 +126,7 @@ __global__ __launch_bounds__(512) void adaln_norm_kernel(
         float y[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) y[e] = v[r][i][e] * rs * sa[e] + sb[e];
-        orow[c] = pack8(y);
+        store_row<T>(orow + c, pack8(y));
       }
     }
   }
@@ -167,7 +181,7 @@ __global__ __launch_bounds__(512) void rms_gain_kernel(const T* in, bf16_t* out,
         float y[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) y[e] = v[r][i][e] * rs * g[e];
-        orow[c] = pack8(y);
+        store_row<T>(orow + c, pack8(y));
       }
     }
   }
@@ -375,7 +389,7 @@ __device__ __forceinline__ void qk_norm_rope_group(const QkRopeParams& p, int gr
           y[2 * e] = x0 * cc[e] - x1 * ss[e];
           y[2 * e + 1] = x0 * ss[e] + x1 * cc[e];
         }
-        qo[c] = pack8(y);
+        store_stream(qo + c, pack8(y));
         const float4 k0 = lg_k[c], k1 = lg_k[nchunk + c];
         const float gk[8] = {k0.x, k0.y, k0.z, k0.w, k1.x, k1.y, k1.z, k1.w};
         unpack8(kraw[r][i], a);
@@ -388,7 +402,7 @@ __device__ __forceinline__ void qk_norm_rope_group(const QkRopeParams& p, int gr
         if (page >= 0) {
           bf16_t* dst =
               p.k_pages + ((static_cast<size_t>(page) * p.H + h) * p.T + off) * p.hd + e0;
-          *reinterpret_cast<uint4*>(dst) = pack8(y);
+          store_stream(reinterpret_cast<uint4*>(dst), pack8(y));
         }
       }
     }
@@ -569,9 +583,31 @@ __device__ __forceinline__ void v_append16_block(const VtParams& p, int nb, int 
   }
 }
 
-__global__ __launch_bounds__(256) void v_append16_kernel(const VtParams p) {
+// Value tile of workgroup w: each XCD takes a run of tiles, token blocks of one
+// head in order.  The 128-byte pieces that neighbouring token blocks write to a
+// transposed row share its cache lines (rows are not whole lines long), and
+// only within one XCD's L2 do the two halves of a line meet before they are
+// written out: with neighbours on different XCDs the appends of 14040 tokens,
+// 1536 wide, took 70 us, so 64, and with streaming stores of q and k 62 us
+// (4.2 TB/s).  false: no tile.
+__device__ __forceinline__ bool v_tile(int w, int v_blocks, int H, int& nb, int& h) {
+  const int total = v_blocks * H, per = (total + kNumXcd - 1) / kNumXcd;
+  const int v = (w % kNumXcd) * per + w / kNumXcd;
+  if (w / kNumXcd >= per || v >= total) return false;
+  h = v / v_blocks;
+  nb = v - h * v_blocks;
+  return true;
+}
+// workgroups v_tile spreads the tiles over
+static int v_tile_groups(int v_blocks, int H) {
+  return (v_blocks * H + kNumXcd - 1) / kNumXcd * kNumXcd;
+}
+
+__global__ __launch_bounds__(256) void v_append16_kernel(const VtParams p, int v_blocks) {
   __shared__ __attribute__((aligned(16))) bf16_t tile[kVaRows][128];
-  v_append16_block(p, blockIdx.x, blockIdx.y, tile);
+  int nb, h;
+  if (!v_tile(blockIdx.x, v_blocks, p.H, nb, h)) return;
+  v_append16_block(p, nb, h, tile);
 }
 
 // The key path (QK-norm + RoPE + key append) and the 16-byte value append in
@@ -587,8 +623,9 @@ __global__ __launch_bounds__(256) void qk_v_append_kernel(const QkRopeParams qp,
   if (b < qk_groups) {
     qk_norm_rope_group<MAXC>(qp, b, lds_qkv);
   } else {
-    const int v = b - qk_groups;
-    v_append16_block(vp, v % v_blocks, v / v_blocks, reinterpret_cast<bf16_t (*)[128]>(lds_qkv));
+    int nb, h;
+    if (!v_tile(b - qk_groups, v_blocks, vp.H, nb, h)) return;
+    v_append16_block(vp, nb, h, reinterpret_cast<bf16_t (*)[128]>(lds_qkv));
   }
 }
 
@@ -631,8 +668,8 @@ hipError_t launch_v_transpose(hipStream_t st, const bf16_t* src, int ld_src, int
   const VtParams p = vt_params(src, ld_src, col_off, N, D, H, hd, dst, paged, T, page_table,
                                max_frames, n_pages, rs);
   if (vt_groups8(p))
-    hipLaunchKernelGGL(v_append16_kernel, dim3((N + kVaRows - 1) / kVaRows, H), dim3(256), 0, st,
-                       p);
+    hipLaunchKernelGGL(v_append16_kernel, dim3(v_tile_groups((N + kVaRows - 1) / kVaRows, H)), dim3(256), 0,
+                       st, p, (N + kVaRows - 1) / kVaRows);
   else
     hipLaunchKernelGGL(v_transpose_kernel, dim3((N + kVtRows - 1) / kVtRows, H), dim3(256), 0,
                        st, p);
@@ -656,7 +693,7 @@ hipError_t launch_kv_append(hipStream_t st, const bf16_t* qkv, int N, const Rope
   const QkRopeParams qp = qk_params(qkv, N, g, g_q, g_k, q_out, k_pages, page_table, rs);
   const int qk_groups = (N + kRowsPerGroup - 1) / kRowsPerGroup;
   const int v_blocks = (N + kVaRows - 1) / kVaRows;
-  const dim3 grid(qk_groups + v_blocks * g.H);
+  const dim3 grid(qk_groups + v_tile_groups(v_blocks, g.H));
   const size_t lds = std::max(qk_lds_bytes(g.D), sizeof(bf16_t) * kVaRows * 128);
   switch (mc) {
 #define ARDIT_QKV_CASE(C)                                                                     \

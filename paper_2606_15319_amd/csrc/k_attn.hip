@@ -812,6 +812,187 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const AttnArgs a) {
   }
 }
 
+// Attention over few keys for few queries.  An item of attn_kernel walks its
+// tiles one after the other (about 1.7 us each) on one CU, and small calls have
+// a handful of items.  Here a workgroup takes 32 queries of one (stream, head)
+// and its eight waves take every eighth key tile, so a call of H heads and q
+// queries spreads over H q / 32 CUs and each wave walks n_tiles / 8 tiles.  A
+// wave reads its K and V fragments straight from memory (the tiles are not
+// shared between waves, so LDS would add a trip and two barriers), in the
+// layouts attn_kernel reads from LDS; the waves' partial results meet in LDS at
+// the end.  192 queries over 576 keys, 4 heads of 64 (the tiny block): 15.9 us
+// on one workgroup per item, 9.5 here; 480 over 1440, 12 heads of 128: 47.8, 25.7.
+// What bounds it is the fragment loads (32 KB a wave and tile in 64-byte
+// pieces, about 5 us for the eight waves' tiles at d = 128).
+constexpr int SM_BQ = 32;      // queries per workgroup
+constexpr int SM_WAVES = 8;
+constexpr int SM_TILES = 64;   // most key tiles of a stream
+
+template <int HD, bool PAGED, bool VEC>
+__global__ __launch_bounds__(64 * SM_WAVES, 1) void attn_small_kernel(const AttnArgs a) {
+  constexpr int KS = HD / 32, DB = HD / 16;
+  __shared__ __attribute__((aligned(16))) float part[SM_WAVES][SM_BQ][HD];
+  __shared__ float part_m[SM_WAVES][SM_BQ], part_l[SM_WAVES][SM_BQ];
+  const int pid = blockIdx.x;
+  const int L = (pid % kNumXcd) * a.per_xcd + pid / kNumXcd;
+  if (L >= a.total_items) return;
+  int si = 0;
+  for (int i = 1; i < a.n_streams; ++i)
+    if (L >= a.s[i].item_begin) si = i;
+  const AttnStream S = a.s[si];
+  const int it = L - S.item_begin;
+  const int h = it / S.n_qtiles, qt = it - h * S.n_qtiles;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, g = lane >> 4;
+  const int kv_len = S.kv_len, vstride = PAGED ? a.T : S.T;
+  const float c = a.scale_log2;
+
+  bf16x8 qf[2][KS];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    const int q_row = min(qt * SM_BQ + 16 * qb + l16, S.q_len - 1);
+    const bf16_t* qp = a.q + static_cast<size_t>(S.q_off + q_row) * a.ldq + h * HD;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const bf16x8*>(qp + 32 * ks + 8 * g);
+  }
+  f32x4 o[2][DB];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o[qb][db][v] = 0.f;
+  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
+
+  for (int t = wave; t < S.n_tiles; t += SM_WAVES) {
+    const int j0 = t * BKV;
+    const TileMap tm = map_tile<HD, PAGED>(a, S, h, j0);
+    bf16x8 kf[4][KS], vf[2][DB];
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      // keys past the end read the stream's last key and are masked below
+      const int o_ = min(tm.off0 + kappa16(kb, l16), tm.off0 + kv_len - 1 - j0);
+      const bf16_t* p = o_ < tm.T ? tm.k0 + static_cast<size_t>(o_) * HD
+                                  : tm.k1 + static_cast<size_t>(o_ - tm.T) * HD;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kf[kb][ks] = *reinterpret_cast<const bf16x8*>(p + 32 * ks + 8 * g);
+    }
+#pragma unroll
+    for (int ps = 0; ps < 2; ++ps) {
+      const int o_ = tm.off0 + 32 * ps + 8 * g, jv = j0 + 32 * ps + 8 * g;
+      const bf16_t* vb = (o_ < tm.T ? tm.v0 + o_ : tm.v1 + (o_ - tm.T)) + static_cast<size_t>(l16) * vstride;
+      if (VEC && jv + 8 <= kv_len) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+          vf[ps][db] = *reinterpret_cast<const bf16x8*>(vb + static_cast<size_t>(16 * db) * vstride);
+      } else {   // values past the end are zero
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+          uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (jv + e < kv_len)
+              w[e >> 1] |= static_cast<uint32_t>(vb[static_cast<size_t>(16 * db) * vstride + e]) << (16 * (e & 1));
+          vf[ps][db] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
+        }
+      }
+    }
+    f32x4 s[4][2];
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s[kb][qb][v] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          s[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][ks], qf[qb][ks], s[kb][qb], 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (j0 + kappa16(kb, 4 * g + v) >= kv_len) s[kb][qb][v] = -INFINITY;
+      }
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      float mx = -INFINITY;
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) mx = fmaxf(mx, s[kb][qb][v]);
+      const float m_new = fmaxf(m_run[qb], rows4_max(mx) * c);
+      const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
+      m_run[qb] = m_new;
+      l_run[qb] *= alpha;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[qb][db][v] *= alpha;
+      bf16x8 pf[2];
+#pragma unroll
+      for (int ps = 0; ps < 2; ++ps) {
+        uint32_t pw[4];
+        const bf16x2 one2 = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
+#pragma unroll
+        for (int e2 = 0; e2 < 4; ++e2) {
+          const int e = 2 * e2;
+          const float p0 = __builtin_amdgcn_exp2f(fmaf(s[2 * ps + (e >> 2)][qb][e & 3], c, -m_new));
+          const float p1 = __builtin_amdgcn_exp2f(fmaf(s[2 * ps + ((e + 1) >> 2)][qb][(e + 1) & 3], c, -m_new));
+          pw[e2] = pack_bf16x2(p0, p1);
+          l_run[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pw[e2]), one2, l_run[qb], false);
+        }
+        pf[ps] = __builtin_bit_cast(bf16x8, u32x4{pw[0], pw[1], pw[2], pw[3]});
+      }
+#pragma unroll
+      for (int ps = 0; ps < 2; ++ps)
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+          o[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[ps][db], pf[ps], o[qb][db], 0, 0, 0);
+    }
+  }
+
+  // merge: o = sum_w 2^(m_w - M) o_w / sum_w 2^(m_w - M) l_w (a wave without
+  // tiles holds m = -inf and adds nothing)
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    const float l_tot = rows4_sum(l_run[qb]);
+    const int row = 16 * qb + l16;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)   // 16-byte chunks XOR-swizzled by row over the banks
+      *reinterpret_cast<float4*>(&part[wave][row][4 * ((4 * db + g) ^ (l16 & 15))]) =
+          make_float4(o[qb][db][0], o[qb][db][1], o[qb][db][2], o[qb][db][3]);
+    if (g == 0) {
+      part_m[wave][row] = m_run[qb];
+      part_l[wave][row] = l_tot;
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < SM_BQ * HD / 4; i += 64 * SM_WAVES) {
+    const int row = i / (HD / 4), c4 = i % (HD / 4);
+    const int ql = qt * SM_BQ + row;
+    if (ql >= S.q_len) continue;
+    float M = part_m[0][row];
+#pragma unroll
+    for (int w = 1; w < SM_WAVES; ++w) M = fmaxf(M, part_m[w][row]);
+    float l = 0.f;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < SM_WAVES; ++w) {
+      if (w >= S.n_tiles) break;   // (that wave had no tile)
+      const float wgt = __builtin_amdgcn_exp2f(part_m[w][row] - M);
+      const float4 p = *reinterpret_cast<const float4*>(&part[w][row][4 * (c4 ^ (row & 15))]);
+      l += wgt * part_l[w][row];
+      acc.x += wgt * p.x;
+      acc.y += wgt * p.y;
+      acc.z += wgt * p.z;
+      acc.w += wgt * p.w;
+    }
+    const float inv = 1.0f / l;
+    uint2 w;
+    w.x = pack_bf16x2(acc.x * inv, acc.y * inv);
+    w.y = pack_bf16x2(acc.z * inv, acc.w * inv);
+    *reinterpret_cast<uint2*>(a.o + static_cast<size_t>(S.q_off + ql) * a.ldo + h * HD + 4 * c4) = w;
+  }
+}
+
 // Block-sparse attention: one workgroup per item over the item's kept tiles,
 // read from its list (written by the block selection).
 template <int HD>
@@ -1012,22 +1193,51 @@ void plan_attention(AttnArgs& a, int head_dim, float* split_ws) {
   }
   a.n_streams = n;
   a.total_items = items;
+  a.small = 0;
   a.total_tiles = 0;
   a.split_blocks = 0;
   a.split_tiles = 0;
   a.part_o = nullptr;
   a.part_ml = nullptr;
+  // Few queries over few keys: 32-query workgroups while they fit one round of
+  // the CUs and the longest stream has at most 64 tiles, eight per wave.  At 240
+  // workgroups (40 heads, 192 queries) 9 tiles take 16.5 us for 22.4 and 24 take
+  // 31 for 48; at 180 (12 heads, 480 queries) 60 tiles 54 for 109.  Past one
+  // round it loses: 480 workgroups 52 us for 36 (60 tiles), 576: 84 for 49 (24).
+  {
+    int64_t wgs = 0;
+    int most = 0;
+    for (int i = 0; i < n; ++i) {
+      wgs += static_cast<int64_t>((tmp[i].q_len + SM_BQ - 1) / SM_BQ) * a.H;
+      most = tmp[i].n_tiles > most ? tmp[i].n_tiles : most;
+    }
+    if (items > 0 && wgs <= kAttnSplitBlocks && most <= SM_TILES) {
+      a.small = 1;
+      a.total_items = static_cast<int32_t>(wgs);
+      a.per_xcd = (a.total_items + kNumXcd - 1) / kNumXcd;
+      int begin = 0;
+      for (int i = 0; i < n; ++i) {
+        tmp[i].n_qtiles = (tmp[i].q_len + SM_BQ - 1) / SM_BQ;
+        tmp[i].item_begin = begin;
+        begin += tmp[i].n_qtiles * a.H;
+        a.s[i] = tmp[i];
+      }
+      return;
+    }
+  }
   // Split when the items fit one round of workgroups but leave more than a
   // quarter of them idle: every item keeps its first W tiles (W = the even
   // share of all tiles per workgroup) and the idle workgroups take equal ranges
   // of the remaining tails.  Items of one head still run their main parts in
   // step, sharing key tiles through L2.  The tail ranges cost more per tile
   // (short segments, partial writes, the merge), which outweighs the gain when
-  // few workgroups are idle.
-  const int spare = kAttnSplitBlocks - items;
-  if (split_ws && items > 0 && spare * 4 > kAttnSplitBlocks &&
-      work >= 8 * static_cast<int64_t>(kAttnSplitBlocks) && work < (static_cast<int64_t>(1) << 30)) {
-    const int W = static_cast<int>((work + kAttnSplitBlocks - 1) / kAttnSplitBlocks);
+  // few workgroups are idle.  The round is cut to as many workgroups as have
+  // eight tiles each (a multiple of the XCDs; 1440 queries over 4320 keys, 4 heads
+  // of 64, 1632 tiles on 24 items: 92 us unsplit, 34 on 200 workgroups).
+  const int blocks = static_cast<int>(min(static_cast<int64_t>(kAttnSplitBlocks), work / 8 / kNumXcd * kNumXcd));
+  const int spare = blocks - items;
+  if (split_ws && items > 0 && spare * 4 > blocks && work < (static_cast<int64_t>(1) << 30)) {
+    const int W = static_cast<int>((work + blocks - 1) / blocks);
     int64_t tails = 0;
     for (int i = 0; i < n; ++i) {
       tmp[i].main_tiles = min(tmp[i].n_tiles, W);
@@ -1035,12 +1245,12 @@ void plan_attention(AttnArgs& a, int head_dim, float* split_ws) {
       tails += static_cast<int64_t>(tmp[i].n_qtiles) * a.H * (tmp[i].n_tiles - tmp[i].main_tiles);
     }
     if (tails > 0) {
-      a.split_blocks = kAttnSplitBlocks;
+      a.split_blocks = blocks;
       a.total_tiles = static_cast<int32_t>(tails);
       a.split_tiles = static_cast<int32_t>((tails + spare - 1) / spare);
       a.part_o = split_ws;
       a.part_ml = split_ws + static_cast<size_t>(2) * kAttnSplitBlocks * BQ * head_dim;
-      a.per_xcd = kAttnSplitBlocks / kNumXcd;
+      a.per_xcd = blocks / kNumXcd;
     } else {
       for (int i = 0; i < n; ++i) tmp[i].main_tiles = tmp[i].n_tiles;
     }
@@ -1051,7 +1261,9 @@ void plan_attention(AttnArgs& a, int head_dim, float* split_ws) {
 
 template <int HD, bool P, bool V>
 static void launch_attn_t(hipStream_t st, const AttnArgs& a, dim3 grid) {
-  if (a.split_blocks) {
+  if (a.small) {
+    hipLaunchKernelGGL((attn_small_kernel<HD, P, V>), grid, dim3(64 * SM_WAVES), 0, st, a);
+  } else if (a.split_blocks) {
     hipLaunchKernelGGL((attn_split_kernel<HD, P, V>), grid, dim3(NTHR), 0, st, a);
     hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3(a.total_items * (BQ / (256 / (HD / 4)))),
                        dim3(256), 0, st, a);

@@ -80,6 +80,7 @@ struct AttnArgs {
   int32_t per_xcd;       // workgroups per XCD (grid = per_xcd * kNumXcd)
   int32_t xcd_begin[kNumXcd + 1];  // one workgroup per item: XCD x runs items
                                    // [xcd_begin[x], xcd_begin[x + 1]), in order
+  int32_t small;         // items of 32 queries, the keys split between a workgroup's waves
   int32_t split_blocks;  // 0: one workgroup per item; else the workgroups of a split schedule
   int32_t total_tiles;   // split: tail tiles of all items, concatenated
   int32_t split_tiles;   // split: tail tiles per spare workgroup

@@ -98,3 +98,44 @@ def test_block_small_products(A, dim, heads, lat_h, lat_w):
     _sync()
     ref = run.reference(0)
     parity(host_f32(run.out), ref["out"], f"block {dim}")
+
+
+# 32-query workgroups with the keys split between waves: up to 256 workgroups
+# and 64 key tiles; past either the items run whole or on a split schedule.
+@pytest.mark.parametrize("hd,q_lens,caches", [
+    (64, [1, 33], [0, 512]),            # one query, one key; 9 tiles: a wave takes two
+    (128, [31, 64, 5], [448, 64, 0]),   # 8 tiles and a ragged end, lengths off every multiple
+    (128, [64], [4032]),                # 64 tiles: the longest taken
+    (128, [64], [4096]),                # 65 tiles, 4 items: a split of 32 workgroups
+    (64, [2048, 8], [0, 1920]),         # 260 workgroups: one workgroup per item
+    (64, [700], [3840]),                # 71 tiles on 12 items: a split schedule below 256 workgroups
+])
+def test_attn_few_keys(A, hd, q_lens, caches):
+    from harness import parity
+    from test_gpu_parity import _attn, _attn_case
+    sh = BlockShape(dim=4 * hd, n_heads=4, head_dim=hd, ffn_dim=512, frames=1, lat_h=4, lat_w=8)
+    pc, dims, batch, q, o, qs, ks, vs = _attn_case(A, sh, q_lens, caches, 420)
+    _attn(A, dims, batch, q, pc.kv(A), o)
+    _sync()
+    og, off = host_f32(o), 0
+    for b, n in enumerate(q_lens):
+        ref = O.attention(qs[b], ks[b], vs[b]).reshape(n, -1)
+        parity(og[off:off + n], ref, f"hd {hd} stream {b}", quantum=ref)
+        off += n
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("ctx", [1, 37, 200])
+def test_block_few_text_keys(A, hd, ctx):
+    """Text attention of a small block: lengths that are no multiple of 8 read
+    their values one by one."""
+    import dataclasses
+    from harness import BlockRun, parity
+    from workloads import WORKLOADS
+    sh = BlockShape(dim=256, n_heads=256 // hd, head_dim=hd, ffn_dim=256, frames=1, lat_h=8, lat_w=9)
+    wl = dataclasses.replace(WORKLOADS["tiny"], shape=sh, cache_chunks=(1,), frame_pos0=(1,), ctx_len=ctx)
+    run = BlockRun(wl, A, shuffle_pages_seed=4)
+    run.run()
+    _sync()
+    ref = run.reference(0)
+    parity(host_f32(run.out), ref["out"], f"block hd {hd} ctx {ctx}")

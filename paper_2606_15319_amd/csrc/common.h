@@ -97,6 +97,40 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv& f) {
   return (t + n) >> f.shift;
 }
 
+// 16 bytes per lane from base + off to LDS byte address m0 + 16 * lane.  base
+// and m0 are the same for every lane of the wave and live in scalar
+// registers, so issuing a load costs no vector instruction.
+__device__ __forceinline__ void lds_dma16(const char* base, uint32_t off, uint32_t m0) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2"
+               :: "v"(off), "s"(m0), "s"(base) : "m0");
+}
+
+// A pointer the compiler may hold in vector registers, made scalar (it is the
+// same in every lane).  readfirstlane returns int, so each half goes through
+// uint32_t before it is widened: a low half with bit 31 set must not be
+// sign-extended into the high half.
+__device__ __forceinline__ const char* uniform_ptr(const void* p) {
+  const uint64_t b = reinterpret_cast<uint64_t>(p);
+  const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b >> 32)));
+  const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b)));
+  return reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
+}
+// The same from a 64-bit address per lane.
+__device__ __forceinline__ void lds_dma16(const char* addr, uint32_t m0) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+               :: "v"(addr), "s"(m0) : "m0");
+}
+// 4 bytes per lane to LDS byte address m0 + 4 * lane.
+__device__ __forceinline__ void lds_dma4(const char* base, uint32_t off, uint32_t m0) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, %2"
+               :: "v"(off), "s"(m0), "s"(base) : "m0");
+}
+// LDS byte address of a shared array, in a scalar register.
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(
+      reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const char*)p))));
+}
+
 __device__ __forceinline__ float gelu_tanh(float y) {
   // 0.5 y (1 + tanh z) = y * sigmoid(2 z) = y / (1 + 2^(-2 z log2(e))),
   // z = sqrt(2/pi) (y + 0.044715 y^3): one exp2 and one reciprocal; for large

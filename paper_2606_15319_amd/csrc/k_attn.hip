@@ -9,12 +9,12 @@
 //
 // Work item = (stream, head, 256-query tile): a 512-thread workgroup, eight
 // waves of 32 query rows.  Key tiles of 64 are staged in LDS (keys row-major,
-// values d-major, 16-byte chunks XOR-swizzled across banks) in two buffers,
-// with the global loads of the next two tiles in flight in registers.  Per
-// wave and tile:
+// values d-major, 16-byte chunks XOR-swizzled across banks) in four slots, by
+// direct loads three tiles ahead.  Per wave and tile:
 //   S^T = K Q^T   on v_mfma_f32_16x16x32_bf16 (K from LDS, Q held in VGPRs),
 //   online softmax in fp32 with exp2 (log2(e)/sqrt(d) folded into one FMA),
-//   O^T += V^T P^T on the same MFMA, P taken straight from the S registers.
+//   O^T += V^T P^T on the same MFMA, P taken straight from the S registers,
+// the two waves of a SIMD half a tile apart (attn_range).
 // Computing the transposed products puts one query row in each lane column,
 // so the row max needs two cross-lane exchanges and no LDS round trip.  The
 // keys of a tile are stored in LDS in the order kappa16 below, which makes
@@ -31,6 +31,8 @@
 #include <math.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "launch.h"
 
 namespace ardit {
@@ -41,6 +43,7 @@ constexpr int BQ = 256;        // queries per work item
 constexpr int BKV = 64;        // keys per tile
 constexpr int NTHR = 512;      // threads per workgroup
 constexpr int LDS_AHEAD = 4;   // fragment reads in flight ahead of the MFMAs
+constexpr int NSLOT = 4;       // key and value tiles in LDS
 
 // Key order of a 64-key tile for 16x16x32 MFMAs: row r of 16-key block kb
 // holds physical key kappa(kb, r) = 32 (kb/2) + 8 (r/4) + 4 (kb%2) + r%4, so
@@ -48,11 +51,6 @@ constexpr int LDS_AHEAD = 4;   // fragment reads in flight ahead of the MFMAs
 // 32 s + 8 g .. 32 s + 8 g + 7 (g = lane / 16): the P operand of PV step s.
 __device__ __forceinline__ int kappa16(int kb, int r) {
   return 32 * (kb >> 1) + 8 * (r >> 2) + 4 * (kb & 1) + (r & 3);
-}
-// LDS row that holds physical key p of the tile
-__device__ __forceinline__ int kappa16_inv(int p) {
-  const int ps = p >> 5, g = (p >> 3) & 3, hh = (p >> 2) & 1, i = p & 3;
-  return 16 * (2 * ps + hh) + 4 * g + i;
 }
 // 16-byte chunk c of LDS row r sits at chunk c ^ swz(r): 16 consecutive rows
 // then cover every bank for a fixed c.  Rows of 256 bytes (keys, d = 128) use
@@ -102,61 +100,6 @@ __device__ __forceinline__ TileMap map_tile(const AttnArgs& a, const AttnStream&
     m.T = 0x7fffffff;   // never crossed
   }
   return m;
-}
-
-// VEC: values of 8 consecutive keys are one aligned 16-byte load (frame pages;
-// text blocks whose length is a multiple of 8).  GUARD: the tile holds keys at
-// or past kv_len (last tile only); those are loaded as zeros.
-template <int HD, bool VEC, bool GUARD, int NK, int NV>
-__device__ __forceinline__ void load_tile(const TileMap& m, int vstride, int j0, int kv_len,
-                                          const int (&k_row)[NK], int k_cc, const int (&v_dd)[NV],
-                                          int v_kc, u32x4 (&rk)[NK], u32x4 (&rv)[NV]) {
-  const u32x4 zero4 = {0u, 0u, 0u, 0u};
-#pragma unroll
-  for (int i = 0; i < NK; ++i) {
-    const int o = m.off0 + k_row[i];
-    const bf16_t* p = (o < m.T ? m.k0 + static_cast<size_t>(o) * HD
-                               : m.k1 + static_cast<size_t>(o - m.T) * HD) + k_cc * 8;
-    if (!GUARD || j0 + k_row[i] < kv_len)
-      rk[i] = *reinterpret_cast<const u32x4*>(p);
-    else
-      rk[i] = zero4;
-  }
-  const int o = m.off0 + 8 * v_kc;
-  const bf16_t* vb = o < m.T ? m.v0 + o : m.v1 + (o - m.T);
-  const int jv = j0 + 8 * v_kc;
-  if (VEC && (!GUARD || jv + 8 <= kv_len)) {
-#pragma unroll
-    for (int i = 0; i < NV; ++i)
-      rv[i] = *reinterpret_cast<const u32x4*>(vb + static_cast<size_t>(v_dd[i]) * vstride);
-  } else {
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        if (jv + e < kv_len) {
-          const uint32_t x = vb[static_cast<size_t>(v_dd[i]) * vstride + e];
-          w[e >> 1] |= x << (16 * (e & 1));
-        }
-      }
-      rv[i] = u32x4{w[0], w[1], w[2], w[3]};
-    }
-  }
-}
-
-// Tile inside one page (the common case): uniform bases plus per-lane byte
-// offsets fixed for the whole kernel, so each load is scalar base + 32-bit
-// vector offset with no per-tile address arithmetic.
-template <int NK, int NV>
-__device__ __forceinline__ void load_tile_fast(const char* kb, const char* vb,
-                                               const uint32_t (&k_off)[NK],
-                                               const uint32_t (&v_off)[NV], u32x4 (&rk)[NK],
-                                               u32x4 (&rv)[NV]) {
-#pragma unroll
-  for (int i = 0; i < NK; ++i) rk[i] = *reinterpret_cast<const u32x4*>(kb + k_off[i]);
-#pragma unroll
-  for (int i = 0; i < NV; ++i) rv[i] = *reinterpret_cast<const u32x4*>(vb + v_off[i]);
 }
 
 // Normalised bf16 output of one item.
@@ -211,41 +154,52 @@ __device__ __forceinline__ void store_partial(const AttnArgs& a, size_t slot,
 // workgroup's 256 queries, then writes the normalised output (slot < 0) or
 // the partial results into slot `slot`.  LIST: positions [tb, te) index the
 // tile list tl (block-sparse attention) instead of being the tiles themselves.
+//
+// What bounds it: the matrix pipe (64 MFMAs of 16 clocks a wave and tile), the
+// issue port that MFMAs (8 clocks each) and vector instructions (4; exponentials
+// 8) share, and, on long calls, the card's power.  Two waves share a SIMD, w and
+// w + 4.  When all eight met at a barrier every tile they ran in step: both in
+// the products, then both in the softmax, about 4000 clocks a tile where the
+// products take 2048.  So the two halves of the workgroup are a half tile
+// apart.  A position's work is an MFMA phase (O += V P of the position before,
+// then S = K Q: no softmax in between) and a VALU phase (its softmax, and the
+// requests for tiles to come); each wave meets one barrier a position, group 0
+// before its MFMA phase and group 1 before its VALU phase, so between two
+// barriers one group runs MFMA then VALU and the other VALU then MFMA.
+// s_setprio lets the MFMA phase issue first: its partner's vector instructions
+// fit in the other half of the port.
+// Tiles arrive by direct global -> LDS loads (no registers: with the staged
+// tiles in them the loop spilled, and every reload waited for the tiles in
+// flight) into four slots each, as pairs: pair u is the keys of position u and
+// the values of u - 1.  Interval t (after barrier t) reads pair t and requests
+// pair t + 3, whose slots were last read in interval t - 1; pair t + 1 is
+// waited for before barrier t + 1.  Page ids and list entries of 64 frames or
+// positions ride in one vector register, a lane each, so that the loop makes no
+// scalar load: an LDS wait would have to cover it.
+// Measured, in turn on one card: 4680 queries over 14040 keys, 12 heads, 386 ->
+// 348 us; over 37440 keys, 20 heads, 2010 -> 1770; the 1.3B-class block step 1405
+// -> 1290, the large one 6060 -> 5640; two barriers a tile (a strict exchange of
+// phases) 352 / 1780 / 1295 / 5650; without s_setprio 1-2% slower.  Reading six
+// or eight fragments ahead instead of four, or one branch for both query
+// blocks' rescaling, changed nothing.
 template <int HD, bool PAGED, bool VEC, bool LIST = false>
 __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& S, int h, int qt,
-                                           int tb, int te, bf16_t (&sK)[2][BKV * HD],
-                                           bf16_t (&sV)[2][HD * BKV], int64_t slot,
+                                           int tb, int te, bf16_t (&sK)[NSLOT * BKV * HD],
+                                           bf16_t (&sV)[NSLOT * HD * BKV], int64_t slot,
                                            const int32_t* tl = nullptr) {
   constexpr int KLD = HD;              // LDS row of the key tile
   constexpr int VLD = BKV;             // LDS row of the value tile
-  constexpr int NK = BKV * HD / 8 / NTHR;   // 16-byte key chunks per thread per tile
-  constexpr int NV = HD * BKV / 8 / NTHR;   // 16-byte value chunks per thread per tile
+  constexpr int TILE = BKV * HD;       // elements of a key or value tile
+  constexpr int NI = TILE * 2 / 1024 / 8;   // 1 KB loads per wave of a key or value tile
   constexpr int KS = HD / 32;          // 16x16x32 MFMA k-steps over d
   constexpr int DB = HD / 16;          // 16-wide output blocks over d
-  static_assert(NK >= 1 && NV >= 1 && 4 * KS > LDS_AHEAD && 2 * DB > LDS_AHEAD, "tile shape");
+  static_assert(4 * KS >= LDS_AHEAD && 2 * DB >= LDS_AHEAD && NTHR == 512, "tile shape");
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
+  const int grp = wave >> 2;   // waves w and w + 4 share a SIMD: one of each group
+  const int n = te - tb;
 
-  // K chunk i of this thread: key row k_row[i], 16-byte column k_cc
-  constexpr int CPR = HD / 8;
-  const int k_cc = tid % CPR;
-  int k_row[NK], k_lds[NK];
-#pragma unroll
-  for (int i = 0; i < NK; ++i) {
-    const int kr = (tid + NTHR * i) / CPR;
-    k_row[i] = kr;
-    const int R = kappa16_inv(kr);
-    k_lds[i] = R * KLD + 8 * (k_cc ^ swz<HD * 2>(R));
-  }
-  // V chunk i: dim v_dd[i], keys 8 * v_kc .. + 8
-  const int v_kc = tid & 7;
-  int v_dd[NV], v_lds[NV];
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    v_dd[i] = (tid + NTHR * i) >> 3;
-    v_lds[i] = v_dd[i] * VLD + 8 * (v_kc ^ swz<BKV * 2>(v_dd[i]));
-  }
   // fragment read offsets: rows kb * 16 + l16 / db * 16 + l16 share the swizzle of l16
   int k_frag[KS], v_frag[2];
 #pragma unroll
@@ -268,16 +222,9 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
 
   const int kv_len = S.kv_len;
   const int vstride = PAGED ? a.T : S.T;   // distance between value dims
+  const int nfull = kv_len / BKV;          // tiles whose 64 keys are all valid
 
-  u32x4 rk[2][NK], rv[2][NV];
-  // byte offsets of this thread's chunks relative to the tile's first key
-  uint32_t k_off[NK], v_off[NV];
   f32x4 o[2][DB];
-#pragma unroll
-  for (int i = 0; i < NK; ++i) k_off[i] = static_cast<uint32_t>((k_row[i] * HD + k_cc * 8) * 2);
-#pragma unroll
-  for (int i = 0; i < NV; ++i)
-    v_off[i] = static_cast<uint32_t>((v_dd[i] * vstride + 8 * v_kc) * 2);
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
@@ -286,311 +233,200 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
       for (int v = 0; v < 4; ++v) o[qb][db][v] = 0.f;
   float m_run[2] = {-INFINITY, -INFINITY};   // running max (scaled, log2) of the lane's rows
   float l_run[2] = {0.f, 0.f};               // this lane's quarter of each running denominator
+  f32x4 s[4][2];
+  bf16x8 pf[2][2];
 
-  const int nfull = kv_len / BKV;         // tiles whose 64 keys are all valid
+  // ---- staging.  Load j of this wave fills LDS rows of 1 KB: of a key tile the
+  // rows R0 .. R0 + 1024 / (2 HD), R0 = (wave NI + j) 1024 / (2 HD), lane i the
+  // 16-byte slot i % CPR of its row, which holds chunk (i % CPR) ^ swz(row) of
+  // key kappa(row); of a value tile dims 8 (wave + 8 j) .. + 8, lane i slot
+  // i % 8 of dim i / 8, chunk (i % 8) ^ swz(dim) (the same for every j).
+  constexpr int CPR = HD / 8;
+  constexpr int KROWS = 64 / CPR;
+  uint32_t k_off[NI];       // byte offset from the tile's first key
+  int k_key[NI];            // first key of the load's rows (d = 128: 4 aligned keys, one page)
+  int k_lane_key[NI];       // this lane's key (d = 64: the rows may lie in two pages)
+#pragma unroll
+  for (int j = 0; j < NI; ++j) {
+    const int R = (wave * NI + j) * KROWS + lane / CPR;
+    const int key = kappa16(R >> 4, R & 15);
+    k_lane_key[j] = key;
+    k_key[j] = kappa16((wave * NI + j) * KROWS >> 4, (wave * NI + j) * KROWS & 15);
+    k_off[j] = static_cast<uint32_t>(key * HD * 2 + ((lane % CPR) ^ swz<HD * 2>(R & 15)) * 16);
+  }
+  const int v_dim = 8 * wave + (lane >> 3);
+  const int v_key = 8 * ((lane & 7) ^ swz<BKV * 2>(v_dim));   // first key of this lane's chunk
+  const uint32_t v_off = static_cast<uint32_t>((v_dim * vstride + v_key) * 2);
+  const uint32_t lds_k = lds_address(sK) + wave * NI * 1024u, lds_v = lds_address(sV) + wave * 1024u;
 
-#define ARDIT_LOAD(tile, set)                                                              \
-{                                                                                        \
-  const int j0_ = (tile) * BKV;                                                          \
-  const TileMap tm_ = map_tile<HD, PAGED>(a, S, h, j0_);                                 \
-  if ((tile) < nfull && tm_.off0 + BKV <= tm_.T && VEC)                                  \
-    load_tile_fast(reinterpret_cast<const char*>(tm_.k0 + static_cast<size_t>(tm_.off0) * HD), \
-                   reinterpret_cast<const char*>(tm_.v0 + tm_.off0), k_off, v_off, rk[set], rv[set]); \
-  else if ((tile) < nfull)                                                               \
-    load_tile<HD, VEC, false>(tm_, vstride, j0_, kv_len, k_row, k_cc, v_dd, v_kc, rk[set], rv[set]); \
-  else                                                                                   \
-    load_tile<HD, VEC, true>(tm_, vstride, j0_, kv_len, k_row, k_cc, v_dd, v_kc, rk[set], rv[set]);  \
-}
-#define ARDIT_STORE(buf, set)                                                              \
-{                                                                                        \
-  _Pragma("unroll") for (int i = 0; i < NK; ++i)                                         \
-      *reinterpret_cast<u32x4*>(&sK[buf][k_lds[i]]) = rk[set][i];                        \
-  _Pragma("unroll") for (int i = 0; i < NV; ++i)                                         \
-      *reinterpret_cast<u32x4*>(&sV[buf][v_lds[i]]) = rv[set][i];                        \
-}
-
-  // list entries are clamped into the stream's tiles, so a corrupt list cannot
-  // send the loads outside the pages
-#define ARDIT_TIX(t) (LIST ? min(max(tl[(t)], 0), S.n_tiles - 1) : (t))
-  // two tiles of loads in flight: register set (t - tb) & 1 holds tile t until stored
-  ARDIT_LOAD(ARDIT_TIX(tb), 0);
-  if (tb + 1 < te) ARDIT_LOAD(ARDIT_TIX(tb + 1), 1);
-  ARDIT_STORE(0, 0);
-  __syncthreads();
-  for (int t0 = tb; t0 < te; t0 += 2) {
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const int t = t0 + half;
-      if (t < te) {
-        const int buf = half;
-        if (t + 2 < te) ARDIT_LOAD(ARDIT_TIX(t + 2), half);
-        // S^T = K Q^T: four 16-key blocks x two 16-query blocks, 8 accumulators
-        f32x4 s[4][2];
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-          for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) s[kb][qb][v] = 0.f;
-        {
-          bf16x8 kf[KS][4];
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb)
-              kf[ks][kb] = *reinterpret_cast<const bf16x8*>(&sK[buf][kb * 16 * KLD + k_frag[ks]]);
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-              for (int qb = 0; qb < 2; ++qb)
-                s[kb][qb] =
-                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks][kb], qf[qb][ks], s[kb][qb], 0, 0, 0);
-          // schedule: LDS_AHEAD reads, then one read per pair of MFMAs
-          __builtin_amdgcn_sched_group_barrier(0x100, LDS_AHEAD, 0);
-#pragma unroll
-          for (int i = 0; i < 4 * KS - LDS_AHEAD; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          }
-          __builtin_amdgcn_sched_group_barrier(0x008, 2 * LDS_AHEAD, 0);
+  const int last_frame = PAGED ? min(static_cast<int>(fdiv(static_cast<uint32_t>(kv_len - 1), a.fT)),
+                                     a.max_frames - 1) : 0;
+  const int32_t* pt = PAGED ? a.page_table + static_cast<size_t>(S.stream) * a.max_frames : nullptr;
+  // lane i: page of frame f0 + i, clamped into the pool
+  auto page_window = [&](int f0) __attribute__((always_inline)) {
+    const int p = pt[min(f0 + lane, last_frame)];
+    return p < 0 ? 0 : (p >= a.n_pages ? a.n_pages - 1 : p);
+  };
+  // lane i: list entry b0 + i; entries are clamped into the stream's tiles, so a
+  // corrupt list cannot send the loads outside the pages
+  auto list_window = [&](int b0) __attribute__((always_inline)) {
+    return min(max(tl[tb + min(b0 + lane, n - 1)], 0), S.n_tiles - 1);
+  };
+  const size_t hs = static_cast<size_t>(PAGED ? a.T : S.T) * HD;
+  int lw0 = 0, lw = 0;
+  if (LIST) lw = list_window(0);
+  int fr = -1, pw0 = 0, pw = 0;
+  const char *kp0 = nullptr, *kp1 = nullptr, *vp0 = nullptr, *vp1 = nullptr;
+  if (PAGED) {
+    // (a stream of up to 64 frames needs one window, which does not wait for the list)
+    if (last_frame >= 64) {
+      const int first = LIST ? __builtin_amdgcn_readlane(lw, 0) : tb;
+      pw0 = static_cast<int>(fdiv(static_cast<uint32_t>(first * BKV), a.fT));
+    }
+    pw = page_window(pw0);
+  } else {
+    kp0 = kp1 = reinterpret_cast<const char*>(a.k + static_cast<size_t>(S.base_off) + h * hs);
+    vp0 = vp1 = reinterpret_cast<const char*>(a.v + static_cast<size_t>(S.base_off) + h * hs);
+  }
+  const char* v_prev = nullptr;   // this lane's value address of the position moved to last
+  int off0 = 0;
+  // moves to position u < n: page bases, off0
+  auto move_to = [&](int u) __attribute__((always_inline)) {
+    int id = tb + u;
+    if (LIST) {
+      if (u - lw0 >= 64) {
+        lw0 = u;
+        lw = list_window(u);
+        asm volatile("" : "+v"(lw));   // waited for here, so no later wait has to
+      }
+      id = __builtin_amdgcn_readlane(lw, u - lw0);
+    }
+    const int j0 = id * BKV;
+    off0 = j0;
+    if (PAGED) {
+      const int f = static_cast<int>(fdiv(static_cast<uint32_t>(j0), a.fT));
+      off0 = j0 - f * a.T;
+      if (f != fr) {   // bases of frame f and the next, less the next's offset
+        if (f + 1 - pw0 >= 64) {
+          pw0 = f;
+          pw = page_window(f);
+          asm volatile("" : "+v"(pw));
         }
-        const int tile = ARDIT_TIX(t);
-        if (tile >= nfull) {   // keys past the end (last tile only)
-#pragma unroll
-          for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              const int key = tile * BKV + kappa16(kb, 4 * g + v);
-              if (key >= kv_len) {
-                s[kb][0][v] = -INFINITY;
-                s[kb][1][v] = -INFINITY;
-              }
-            }
-        }
-        // online softmax in scaled log2 units; the running max is raised only when
-        // a row's tile max exceeds it by more than 8 (p <= 2^8 otherwise), so the
-        // O / l rescale is skipped on almost every tile
-        bf16x8 pf[2][2];
-#pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-          float mx = -INFINITY;
-#pragma unroll
-          for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) mx = fmaxf(mx, s[kb][qb][v]);
-          mx = rows4_max(mx) * c;
-          if (__any(mx > m_run[qb] + 8.0f)) {
-            const float m_new = fmaxf(m_run[qb], mx);
-            const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
-            m_run[qb] = m_new;
-            l_run[qb] *= alpha;
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-              for (int v = 0; v < 4; ++v) o[qb][db][v] *= alpha;
-          }
-          const float mr = m_run[qb];
-#pragma unroll
-          for (int ps = 0; ps < 2; ++ps) {
-            uint32_t pw[4];
-            const bf16x2 one2 = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
-#pragma unroll
-            for (int e2 = 0; e2 < 4; ++e2) {
-              const int e = 2 * e2;
-              const float p0 =
-                  __builtin_amdgcn_exp2f(fmaf(s[2 * ps + (e >> 2)][qb][e & 3], c, -mr));
-              const float p1 = __builtin_amdgcn_exp2f(
-                  fmaf(s[2 * ps + ((e + 1) >> 2)][qb][(e + 1) & 3], c, -mr));
-              pw[e2] = pack_bf16x2(p0, p1);
-              l_run[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pw[e2]),
-                                                          one2, l_run[qb], false);
-            }
-            pf[qb][ps] = __builtin_bit_cast(bf16x8, u32x4{pw[0], pw[1], pw[2], pw[3]});
-          }
-        }
-        // O^T += V^T P^T: 16-dim blocks x two query blocks, 16 accumulators
-        {
-          bf16x8 vf[2][DB];
-#pragma unroll
-          for (int ps = 0; ps < 2; ++ps)
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-              vf[ps][db] = *reinterpret_cast<const bf16x8*>(&sV[buf][db * 16 * VLD + v_frag[ps]]);
-#pragma unroll
-          for (int ps = 0; ps < 2; ++ps)
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-              for (int qb = 0; qb < 2; ++qb)
-                o[qb][db] =
-                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[ps][db], pf[qb][ps], o[qb][db], 0, 0, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, LDS_AHEAD, 0);
-#pragma unroll
-          for (int i = 0; i < 2 * DB - LDS_AHEAD; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          }
-          __builtin_amdgcn_sched_group_barrier(0x008, 2 * LDS_AHEAD, 0);
-        }
-        if (t + 1 < te) ARDIT_STORE(buf ^ 1, half ^ 1);
-        __syncthreads();
+        fr = f;
+        const int p0 = __builtin_amdgcn_readlane(pw, f - pw0), p1 = __builtin_amdgcn_readlane(pw, f + 1 - pw0);
+        kp0 = reinterpret_cast<const char*>(a.k + (static_cast<size_t>(p0) * a.H + h) * hs);
+        kp1 = reinterpret_cast<const char*>(a.k + (static_cast<size_t>(p1) * a.H + h) * hs) - 2 * hs;
+        vp0 = reinterpret_cast<const char*>(a.v + (static_cast<size_t>(p0) * a.H + h) * hs);
+        vp1 = reinterpret_cast<const char*>(a.v + (static_cast<size_t>(p1) * a.H + h) * hs) - 2 * a.T;
       }
     }
-  }
-#undef ARDIT_LOAD
-#undef ARDIT_STORE
-#undef ARDIT_TIX
-  if (slot < 0)
-    store_output<HD>(a, S, h, qt, o, l_run);
-  else
-    store_partial<HD>(a, static_cast<size_t>(slot), o, m_run, l_run);
-}
+    return id;
+  };
+  // direct loads of the keys of the current position into slot u % NSLOT, and of
+  // the values of the position before into slot (u - 1) % NSLOT
+  auto dma_keys = [&](int u) __attribute__((always_inline)) {
+    const uint32_t dst = lds_k + static_cast<uint32_t>(u % NSLOT) * (TILE * 2);
+    const ptrdiff_t ko = static_cast<ptrdiff_t>(off0) * (2 * HD);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      if constexpr (HD == 128) {
+        const char* b = (PAGED && off0 + k_key[j] >= a.T ? kp1 : kp0) + ko;
+        lds_dma16(b, k_off[j], dst + 1024u * j);
+      } else {
+        const char* b = (PAGED && off0 + k_lane_key[j] >= a.T ? kp1 : kp0) + ko;
+        lds_dma16(b + k_off[j], dst + 1024u * j);
+      }
+    }
+    const char* vb = (PAGED && off0 + v_key >= a.T ? vp1 : vp0) + 2 * static_cast<ptrdiff_t>(off0);
+    v_prev = vb + v_off;
+  };
+  auto dma_values = [&](int u) __attribute__((always_inline)) {   // of position u
+    const uint32_t dst = lds_v + static_cast<uint32_t>(u % NSLOT) * (TILE * 2);
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+      lds_dma16(v_prev + static_cast<size_t>(j) * 128 * vstride, dst + 8192u * j);
+  };
+  // Pair u: the keys of position u and the values of position u - 1.  At the
+  // range's ends the last tile, when keys run out inside it, and text of odd
+  // length go through registers, zeroed past the end.  (Lane indices are taken
+  // anew there: shared with the main loop they would stay in registers across it.)
+  auto fetch = [&](int u) __attribute__((always_inline)) {
+    if (u > 0 && u <= n) {
+      const int t = LIST ? min(max(tl[tb + u - 1], 0), S.n_tiles - 1) : tb + u - 1;
+      if (VEC && t < nfull) {
+        dma_values(u - 1);
+      } else {
+        int ln = threadIdx.x & 63;
+        asm volatile("" : "+v"(ln));
+        const TileMap m = map_tile<HD, PAGED>(a, S, h, t * BKV);
+        const int dim = 8 * wave + (ln >> 3), key = 8 * ((ln & 7) ^ swz<BKV * 2>(dim));
+        const int o_ = m.off0 + key;
+        const bf16_t* vb = (o_ < m.T ? m.v0 + o_ : m.v1 + (o_ - m.T)) + static_cast<size_t>(dim) * vstride;
+        const int left = kv_len - t * BKV - key;
+        bf16_t* dst = &sV[((u - 1) % NSLOT) * TILE + wave * 512 + ln * 8];
+#pragma unroll 1
+        for (int j = 0; j < NI; ++j)
+#pragma unroll 1
+          for (int e = 0; e < 8; ++e)
+            dst[j * 4096 + e] = e < left ? vb[static_cast<size_t>(64 * j) * vstride + e] : bf16_t(0);
+      }
+    }
+    if (u < n) {
+      const int t = move_to(u);
+      if (t < nfull) {
+        dma_keys(u);
+      } else {   // (a partial tile's values come with the next pair, through registers)
+        int ln = threadIdx.x & 63;
+        asm volatile("" : "+v"(ln));
+        const TileMap m = map_tile<HD, PAGED>(a, S, h, t * BKV);
+#pragma unroll 1
+        for (int j = 0; j < NI; ++j) {
+          const int R = (wave * NI + j) * KROWS + ln / CPR;
+          const int key = kappa16(R >> 4, R & 15), o_ = m.off0 + key;
+          const bf16_t* b = (o_ < m.T ? m.k0 + static_cast<size_t>(o_) * HD : m.k1 + static_cast<size_t>(o_ - m.T) * HD) +
+                            8 * ((ln % CPR) ^ swz<HD * 2>(R & 15));
+          u32x4 x = {0u, 0u, 0u, 0u};
+          if (t * BKV + key < kv_len) x = *reinterpret_cast<const u32x4*>(b);
+          *reinterpret_cast<u32x4*>(&sK[(u % NSLOT) * TILE + (wave * NI + j) * 512 + ln * 8]) = x;
+        }
+      }
+    }
+  };
 
-// One workgroup per item.  The tile loop is the same as attn_range's; it is
-// kept in the kernel itself because routing it through the inlined function
-// changes the register allocation (copies of the output accumulators every
-// tile) and costs about 2% on long key ranges.
-template <int HD, bool PAGED, bool VEC>
-__global__ __launch_bounds__(NTHR, 1) void attn_kernel(const AttnArgs a) {
-  constexpr int KLD = HD;
-  constexpr int VLD = BKV;
-  constexpr int NK = BKV * HD / 8 / NTHR;   // 16-byte key chunks per thread per tile
-  constexpr int NV = HD * BKV / 8 / NTHR;   // 16-byte value chunks per thread per tile
-  constexpr int KS = HD / 32;          // 16x16x32 MFMA k-steps over d
-  constexpr int DB = HD / 16;          // 16-wide output blocks over d
-  __shared__ __attribute__((aligned(16))) bf16_t sK[2][BKV * KLD];
-  __shared__ __attribute__((aligned(16))) bf16_t sV[2][HD * VLD];
-
-  // ---- work item (XCD-aware: each XCD runs a contiguous range of items, so
-  // the items of one head share its L2, the ranges balanced by tile count)
-  const int pid = blockIdx.x;
-  const int xcd = pid % kNumXcd;
-  const int L = a.xcd_begin[xcd] + pid / kNumXcd;
-  if (L >= a.xcd_begin[xcd + 1]) return;
-  int si = 0;
-  for (int i = 1; i < a.n_streams; ++i)
-    if (L >= a.s[i].item_begin) si = i;
-  const AttnStream S = a.s[si];
-  const int it = L - S.item_begin;
-  const int h = it / S.n_qtiles;
-  const int qt = it - h * S.n_qtiles;
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int l16 = lane & 15, g = lane >> 4;
-
-  // ---- Q fragments (B operand of S^T = K Q^T): the wave's 32 rows are two
-  // 16-row blocks; lane holds row l16 of block qb, dims 32 ks + 8 g ..
-  int q_local[2];
-  bf16x8 qf[2][KS];
+  // MFMA phase of position t: O^T += V^T P^T of position t - 1 (pv), then
+  // S^T = K Q^T of position t
+  auto mfma_phase = [&](int t, auto pv_c) __attribute__((always_inline)) {
+    constexpr bool PV = decltype(pv_c)::value;
+    bf16x8 vf[2][DB], kf[KS][4];
+    __builtin_amdgcn_s_setprio(1);
+    if constexpr (PV) {
+      const bf16_t* tv = &sV[((t - 1) % NSLOT) * TILE];
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb) {
-    q_local[qb] = qt * BQ + wave * 32 + 16 * qb + l16;
-    const int q_row = min(q_local[qb], S.q_len - 1);
-    const bf16_t* qp = a.q + static_cast<size_t>(S.q_off + q_row) * a.ldq + h * HD;
+      for (int ps = 0; ps < 2; ++ps)
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      qf[qb][ks] = *reinterpret_cast<const bf16x8*>(qp + 32 * ks + 8 * g);
-  }
-
-  const int kv_len = S.kv_len;
-  const int vstride = PAGED ? a.T : S.T;   // distance between value dims
-
-  // K chunk i of this thread: key row k_row[i], 16-byte column k_cc
-  constexpr int CPR = HD / 8;
-  const int k_cc = tid % CPR;
-  int k_row[NK], k_lds[NK];
+        for (int db = 0; db < DB; ++db)
+          vf[ps][db] = *reinterpret_cast<const bf16x8*>(&tv[db * 16 * VLD + v_frag[ps]]);
 #pragma unroll
-  for (int i = 0; i < NK; ++i) {
-    const int kr = (tid + NTHR * i) / CPR;
-    k_row[i] = kr;
-    const int R = kappa16_inv(kr);
-    k_lds[i] = R * KLD + 8 * (k_cc ^ swz<HD * 2>(R));
-  }
-  // V chunk i: dim v_dd[i], keys 8 * v_kc .. + 8
-  const int v_kc = tid & 7;
-  int v_dd[NV], v_lds[NV];
+      for (int ps = 0; ps < 2; ++ps)
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    v_dd[i] = (tid + NTHR * i) >> 3;
-    v_lds[i] = v_dd[i] * VLD + 8 * (v_kc ^ swz<BKV * 2>(v_dd[i]));
-  }
-  int k_frag[KS], v_frag[2];
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) k_frag[ks] = l16 * KLD + 8 * ((4 * ks + g) ^ swz<HD * 2>(l16));
-#pragma unroll
-  for (int ps = 0; ps < 2; ++ps) v_frag[ps] = l16 * VLD + 8 * ((4 * ps + g) ^ swz<BKV * 2>(l16));
-
-  u32x4 rk[2][NK], rv[2][NV];
-  // byte offsets of this thread's chunks relative to the tile's first key
-  uint32_t k_off[NK], v_off[NV];
-#pragma unroll
-  for (int i = 0; i < NK; ++i) k_off[i] = static_cast<uint32_t>((k_row[i] * HD + k_cc * 8) * 2);
-#pragma unroll
-  for (int i = 0; i < NV; ++i) v_off[i] = static_cast<uint32_t>((v_dd[i] * vstride + 8 * v_kc) * 2);
-  f32x4 o[2][DB];
-#pragma unroll
-  for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) o[qb][db][v] = 0.f;
-  float m_run[2] = {-INFINITY, -INFINITY};   // running max (scaled, log2) of the lane's rows
-  float l_run[2] = {0.f, 0.f};               // this lane's quarter of each running denominator
-  const float c = a.scale_log2;
-
-  const int ntiles = (kv_len + BKV - 1) / BKV;
-  const int nfull = kv_len / BKV;   // tiles whose 64 keys are all valid
-
-#define ARDIT_LOAD(tile, set)                                                              \
-  {                                                                                        \
-    const int j0_ = (tile) * BKV;                                                          \
-    const TileMap tm_ = map_tile<HD, PAGED>(a, S, h, j0_);                                 \
-    if ((tile) < nfull && tm_.off0 + BKV <= tm_.T && VEC)                                  \
-      load_tile_fast(reinterpret_cast<const char*>(tm_.k0 + static_cast<size_t>(tm_.off0) * HD), \
-                     reinterpret_cast<const char*>(tm_.v0 + tm_.off0), k_off, v_off, rk[set], rv[set]); \
-    else if ((tile) < nfull)                                                               \
-      load_tile<HD, VEC, false>(tm_, vstride, j0_, kv_len, k_row, k_cc, v_dd, v_kc, rk[set], rv[set]); \
-    else                                                                                   \
-      load_tile<HD, VEC, true>(tm_, vstride, j0_, kv_len, k_row, k_cc, v_dd, v_kc, rk[set], rv[set]);  \
-  }
-#define ARDIT_STORE(buf, set)                                                              \
-  {                                                                                        \
-    _Pragma("unroll") for (int i = 0; i < NK; ++i)                                         \
-        *reinterpret_cast<u32x4*>(&sK[buf][k_lds[i]]) = rk[set][i];                        \
-    _Pragma("unroll") for (int i = 0; i < NV; ++i)                                         \
-        *reinterpret_cast<u32x4*>(&sV[buf][v_lds[i]]) = rv[set][i];                        \
-  }
-
-  // two tiles of loads in flight: register set (t & 1) holds tile t until stored
-  ARDIT_LOAD(0, 0);
-  if (ntiles > 1) ARDIT_LOAD(1, 1);
-  ARDIT_STORE(0, 0);
-  __syncthreads();
-  for (int t0 = 0; t0 < ntiles; t0 += 2) {
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-    const int t = t0 + half;
-    if (t < ntiles) {
-    const int buf = half;
-    if (t + 2 < ntiles) ARDIT_LOAD(t + 2, half);
-    // S^T = K Q^T: four 16-key blocks x two 16-query blocks, 8 accumulators
-    f32x4 s[4][2];
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-      for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) s[kb][qb][v] = 0.f;
+          for (int qb = 0; qb < 2; ++qb)
+            o[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[ps][db], pf[qb][ps], o[qb][db], 0, 0, 0);
+    }
     {
-      bf16x8 kf[KS][4];
+      const bf16_t* tk = &sK[(t % NSLOT) * TILE];
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) s[kb][qb][v] = 0.f;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
-          kf[ks][kb] = *reinterpret_cast<const bf16x8*>(&sK[buf][kb * 16 * KLD + k_frag[ks]]);
+          kf[ks][kb] = *reinterpret_cast<const bf16x8*>(&tk[kb * 16 * KLD + k_frag[ks]]);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -598,20 +434,29 @@ __global__ __launch_bounds__(NTHR, 1) void attn_kernel(const AttnArgs a) {
 #pragma unroll
           for (int qb = 0; qb < 2; ++qb)
             s[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks][kb], qf[qb][ks], s[kb][qb], 0, 0, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, LDS_AHEAD, 0);
-#pragma unroll
-      for (int i = 0; i < 4 * KS - LDS_AHEAD; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 2 * LDS_AHEAD, 0);
     }
-    if (t >= nfull) {   // keys past the end (last tile only)
+    // schedule: LDS_AHEAD reads, then one read per pair of MFMAs
+    constexpr int NR = (PV ? 2 * DB : 0) + 4 * KS;
+    __builtin_amdgcn_sched_group_barrier(0x100, LDS_AHEAD, 0);
+#pragma unroll
+    for (int i = 0; i < NR - LDS_AHEAD; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 2 * LDS_AHEAD, 0);
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  // softmax of the scores of the current position into pf (ends: the position's
+  // tile may hold keys past the end)
+  auto softmax = [&](const bool ends, const int tile) __attribute__((always_inline)) {
+    if (ends && tile >= nfull) {   // keys past the end (the last position only)
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const int key = t * BKV + kappa16(kb, 4 * g + v);
+          const int key = tile * BKV + kappa16(kb, 4 * g + v);
           if (key >= kv_len) {
             s[kb][0][v] = -INFINITY;
             s[kb][1][v] = -INFINITY;
@@ -621,7 +466,6 @@ __global__ __launch_bounds__(NTHR, 1) void attn_kernel(const AttnArgs a) {
     // online softmax in scaled log2 units; the running max is raised only when
     // a row's tile max exceeds it by more than 8 (p <= 2^8 otherwise), so the
     // O / l rescale is skipped on almost every tile
-    bf16x8 pf[2][2];
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
       float mx = -INFINITY;
@@ -640,6 +484,9 @@ __global__ __launch_bounds__(NTHR, 1) void attn_kernel(const AttnArgs a) {
 #pragma unroll
           for (int v = 0; v < 4; ++v) o[qb][db][v] *= alpha;
       }
+    }
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
       const float mr = m_run[qb];
 #pragma unroll
       for (int ps = 0; ps < 2; ++ps) {
@@ -652,71 +499,106 @@ __global__ __launch_bounds__(NTHR, 1) void attn_kernel(const AttnArgs a) {
 #pragma unroll
         for (int e2 = 0; e2 < 4; ++e2) {
           const int e = 2 * e2;
-          const float p0 = __builtin_amdgcn_exp2f(fmaf(s[2 * ps + (e >> 2)][qb][e & 3], c, -mr));
-          const float p1 =
-              __builtin_amdgcn_exp2f(fmaf(s[2 * ps + ((e + 1) >> 2)][qb][(e + 1) & 3], c, -mr));
+          const float p0 =
+              __builtin_amdgcn_exp2f(fmaf(s[2 * ps + (e >> 2)][qb][e & 3], c, -mr));
+          const float p1 = __builtin_amdgcn_exp2f(
+              fmaf(s[2 * ps + ((e + 1) >> 2)][qb][(e + 1) & 3], c, -mr));
           pw[e2] = pack_bf16x2(p0, p1);
-          l_run[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pw[e2]), one2,
-                                                      l_run[qb], false);
+          l_run[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pw[e2]),
+                                                      one2, l_run[qb], false);
         }
         pf[qb][ps] = __builtin_bit_cast(bf16x8, u32x4{pw[0], pw[1], pw[2], pw[3]});
       }
     }
-    // O^T += V^T P^T: 16-dim blocks x two query blocks, 16 accumulators
-    {
-      bf16x8 vf[2][DB];
-#pragma unroll
-      for (int ps = 0; ps < 2; ++ps)
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-          vf[ps][db] = *reinterpret_cast<const bf16x8*>(&sV[buf][db * 16 * VLD + v_frag[ps]]);
-#pragma unroll
-      for (int ps = 0; ps < 2; ++ps)
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int qb = 0; qb < 2; ++qb)
-            o[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[ps][db], pf[qb][ps], o[qb][db], 0, 0, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, LDS_AHEAD, 0);
-#pragma unroll
-      for (int i = 0; i < 2 * DB - LDS_AHEAD; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 2 * LDS_AHEAD, 0);
-    }
-    if (t + 1 < ntiles) ARDIT_STORE(buf ^ 1, half ^ 1);
-    __syncthreads();
-    }
-    }
-  }
-#undef ARDIT_LOAD
-#undef ARDIT_STORE
+    // the weights and sums are formed here, in this phase
+    asm volatile("" : "+v"(pf[0][0]), "+v"(pf[0][1]), "+v"(pf[1][0]), "+v"(pf[1][1]), "+v"(l_run[0]), "+v"(l_run[1]));
+  };
+  const std::true_type yes;
+  const std::false_type no;
 
-#pragma unroll
-  for (int qb = 0; qb < 2; ++qb) {
-    const float l_tot = rows4_sum(l_run[qb]);
-    const float inv = 1.0f / l_tot;
-    if (q_local[qb] < S.q_len) {
-      bf16_t* op = a.o + static_cast<size_t>(S.q_off + q_local[qb]) * a.ldo + h * HD;
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        uint2 w;
-        w.x = pack_bf16x2(o[qb][db][0] * inv, o[qb][db][1] * inv);
-        w.y = pack_bf16x2(o[qb][db][2] * inv, o[qb][db][3] * inv);
-        *reinterpret_cast<uint2*>(op + 16 * db + 4 * g) = w;
+  // ---- prologue: the pairs ahead of the group's first VALU phase
+#pragma unroll 1
+  for (int u = 0; u < 3 + grp; ++u) fetch(u);
+  if (!VEC || 2 + grp > n - 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  else if (grp == 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * NI) : "memory");   // pair 0 has landed
+  else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(6 * NI) : "memory");
+  __syncthreads();
+  const int last_tile = LIST ? min(max(tl[te - 1], 0), S.n_tiles - 1) : te - 1;
+  // requests pair u
+  auto stage = [&](int u) __attribute__((always_inline)) {
+    if (VEC && u <= n - 2) {   // whole, and so are all before it
+      dma_values(u - 1);
+      move_to(u);
+      dma_keys(u);
+    } else {
+      fetch(u);
+    }
+  };
+  // the pair read after the next barrier has landed; u: the last pair requested
+  auto wait_next = [&](int u) __attribute__((always_inline)) {
+    if (VEC && u <= n - 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * NI) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  };
+  if (qt * BQ + wave * 32 < S.q_len) {
+    mfma_phase(0, no);
+#pragma unroll 1
+    for (int t = 0; t < n; ++t) {
+      if (grp == 1) {
+        wait_next(t + 3);
+        __syncthreads();
       }
+      stage(t + 3 + grp);
+      softmax(t == n - 1, last_tile);
+      if (grp == 0) {
+        wait_next(t + 3);
+        __syncthreads();
+      }
+      mfma_phase(t + 1, yes);   // (past the last position the scores are not used)
+    }
+  } else {   // no query of this wave exists: it only stages
+#pragma unroll 1
+    for (int t = 0; t < n; ++t) {
+      if (grp == 0) stage(t + 3);
+      wait_next(t + 3);
+      __syncthreads();
+      if (grp == 1) stage(t + 4);
     }
   }
+  if (slot < 0)
+    store_output<HD>(a, S, h, qt, o, l_run);
+  else
+    store_partial<HD>(a, static_cast<size_t>(slot), o, m_run, l_run);
+  if (slot >= 0) __syncthreads();   // a following range reuses the tiles
 }
 
+// One workgroup per item.
+template <int HD, bool PAGED, bool VEC>
+__global__ __launch_bounds__(NTHR, 1) void attn_kernel(const AttnArgs a) {
+  __shared__ __attribute__((aligned(16))) bf16_t sK[NSLOT * BKV * HD];
+  __shared__ __attribute__((aligned(16))) bf16_t sV[NSLOT * HD * BKV];
+
+  // ---- work item (XCD-aware: each XCD runs a contiguous range of items, so
+  // the items of one head share its L2, the ranges balanced by tile count)
+  const int pid = blockIdx.x;
+  const int xcd = pid % kNumXcd;
+  const int L = a.xcd_begin[xcd] + pid / kNumXcd;
+  if (L >= a.xcd_begin[xcd + 1]) return;
+  int si = 0;
+  for (int i = 1; i < a.n_streams; ++i)
+    if (L >= a.s[i].item_begin) si = i;
+  const AttnStream S = a.s[si];
+  const int it = L - S.item_begin;
+  const int h = it / S.n_qtiles;
+  const int qt = it - h * S.n_qtiles;
+  attn_range<HD, PAGED, VEC>(a, S, h, qt, 0, S.n_tiles, sK, sV, -1);
+}
 
 // Split schedule: each item runs its first main_tiles tiles in its own
 // workgroup; the remaining workgroups take equal ranges of the concatenated tails.
 template <int HD, bool PAGED, bool VEC>
 __global__ __launch_bounds__(NTHR, 1) void attn_split_kernel(const AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) bf16_t sK[2][BKV * HD];
-  __shared__ __attribute__((aligned(16))) bf16_t sV[2][HD * BKV];
+  __shared__ __attribute__((aligned(16))) bf16_t sK[NSLOT * BKV * HD];
+  __shared__ __attribute__((aligned(16))) bf16_t sV[NSLOT * HD * BKV];
 
   const int pid = blockIdx.x;
   const int xcd = pid % kNumXcd, j = pid / kNumXcd;
@@ -997,8 +879,8 @@ __global__ __launch_bounds__(64 * SM_WAVES, 1) void attn_small_kernel(const Attn
 // read from its list (written by the block selection).
 template <int HD>
 __global__ __launch_bounds__(NTHR, 1) void attn_sparse_kernel(const AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) bf16_t sK[2][BKV * HD];
-  __shared__ __attribute__((aligned(16))) bf16_t sV[2][HD * BKV];
+  __shared__ __attribute__((aligned(16))) bf16_t sK[NSLOT * BKV * HD];
+  __shared__ __attribute__((aligned(16))) bf16_t sV[NSLOT * HD * BKV];
   const int pid = blockIdx.x;
   const int xcd = pid % kNumXcd;
   const int L = a.xcd_begin[xcd] + pid / kNumXcd;

@@ -34,25 +34,6 @@ namespace ardit {
 
 namespace {
 
-// 16 bytes per lane from base + off to LDS byte address m0 + 16 * lane.  base
-// and m0 are the same for every lane of the wave and live in scalar
-// registers, so issuing a load costs no vector instruction.
-__device__ __forceinline__ void lds_dma16(const char* base, uint32_t off, uint32_t m0) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2"
-               :: "v"(off), "s"(m0), "s"(base) : "m0");
-}
-
-// A pointer the compiler may hold in vector registers, made scalar (it is the
-// same in every lane).  readfirstlane returns int, so each half goes through
-// uint32_t before it is widened: a low half with bit 31 set must not be
-// sign-extended into the high half.
-__device__ __forceinline__ const char* uniform_ptr(const void* p) {
-  const uint64_t b = reinterpret_cast<uint64_t>(p);
-  const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b >> 32)));
-  const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b)));
-  return reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
 constexpr int BN = 256, BK = 64, NT = 512;
 constexpr int NWAVES = NT / 64;
 constexpr int WN = 64, NB = WN / 16;

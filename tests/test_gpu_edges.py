@@ -139,3 +139,49 @@ def test_block_few_text_keys(A, hd, ctx):
     _sync()
     ref = run.reference(0)
     parity(host_f32(run.out), ref["out"], f"block hd {hd} ctx {ctx}")
+
+
+@pytest.mark.parametrize("ctx", [1, 64, 100, 192, 264, 448])
+def test_block_text_tiles(A, ctx):
+    """Text attention on 256-query items over 1 to 7 key tiles: fewer than the
+    tiles in flight, whole and partial ends, and a length (100) whose values are
+    not 16-byte aligned."""
+    import dataclasses
+    from harness import BlockRun, parity
+    from workloads import WORKLOADS
+    sh = BlockShape(dim=1024, n_heads=8, head_dim=128, ffn_dim=256, frames=1, lat_h=26, lat_w=40)
+    wl = dataclasses.replace(WORKLOADS["tiny"], shape=sh, cache_chunks=(0,), frame_pos0=(0,), ctx_len=ctx)
+    run = BlockRun(wl, A, shuffle_pages_seed=3)
+    run.run()
+    _sync()
+    ref = run.reference(0)
+    parity(host_f32(run.out), ref["out"], f"ctx {ctx}")
+
+
+@pytest.mark.parametrize("quant", [0, 1])
+@pytest.mark.parametrize("keys", [64, 100, 128, 192, 250, 320, 384])
+def test_attn_sparse_few_tiles(A, quant, keys):
+    """Lists of 1 to 6 tiles (fewer than the pairs in flight), the last one whole
+    or partial, on the bf16 and FP8 kernels: every tile kept but one."""
+    import oracle.sparse_ref as SR
+    from harness import fp8_parity, parity
+    from oracle import fp8_ref
+    from test_gpu_parity import _attn, _attn_case
+    T = 32
+    sh = BlockShape(dim=256, n_heads=2, head_dim=128, ffn_dim=256, frames=1, lat_h=4, lat_w=8)
+    cache = (keys - 1) // T * T
+    q_len = keys - cache
+    pc, dims, batch, q, o, qs, ks, vs = _attn_case(A, sh, [q_len], [cache], 430)
+    n = -(-keys // 64)
+    rho = 1.0 / n if n > 1 else 0.25
+    _attn(A, dims, A.Batch([q_len], [cache], sparsity=[rho], quant=[quant]), q, pc.kv(A), o)
+    _sync()
+    lists = SR.select_blocks(SR.block_scores(qs[0], ks[0]), SR.keep_count(n, rho))
+    got = host_f32(o).reshape(q_len, 2, 128)
+    if quant:
+        mask = np.stack([SR.block_mask(lists[h], q_len, keys) for h in range(2)])
+        ref, _, sigma = fp8_ref.fp8_attention(qs[0], ks[0], vs[0], mask=mask, sigma=True)
+        fp8_parity(got, ref, sigma, f"fp8 {keys}")
+    else:
+        ref = SR.sparse_attention(qs[0], ks[0], vs[0], lists)
+        parity(got, ref, f"keys {keys}", quantum=ref)

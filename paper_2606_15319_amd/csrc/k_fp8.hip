@@ -34,6 +34,8 @@
 // (row / 2) % 4 left two-way conflicts: 7% slower).
 #include <math.h>
 
+#include <type_traits>
+
 #include "launch.h"
 
 namespace ardit {
@@ -211,14 +213,37 @@ __device__ __forceinline__ int f8_lds_row(int p) {
   return 32 * b + 8 * (i >> 2) + 4 * h + (i & 3);
 }
 
+// Key of LDS row R of a tile: the inverse of the order above.
+__device__ __forceinline__ int f8_row_key(int R) {
+  const int r = R & 31;
+  return 32 * (R >> 5) + 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3);
+}
+
+// What bounds it: vector issue (about 190 instructions a wave and tile beside 8
+// MFMAs; exponentials and E4M3 conversions take 8 clocks of the port, most others
+// 4) and how few of them one wave alone can issue.  As in the bf16 kernel the two
+// waves of a SIMD run half a tile apart, one barrier a position, group 0 before
+// its MFMA phase and group 1 before its VALU phase, and tiles arrive as pairs
+// (keys of position u, values of u - 1) by direct loads into four slots.  The
+// phases share the vector work: the conversion and sum of a position's weights
+// stand beside the next position's S MFMAs, its block maxima beside the PV MFMAs,
+// so both waves always have some to issue.  4680 queries over 32760 keys, 12
+// heads, with the quantisation before it (71 us): 807 us in step; 760 with the
+// phases half a tile apart, all vector work in one of them, two barriers a tile;
+// 700 with the work shared; 660 with one barrier.  Scheduling groups (reads
+// first, or vector work between the MFMAs) were 2-5% slower than the compiler's
+// order.
+constexpr int F8_SLOTS = 4;
+
 template <bool LIST>
 __global__ __launch_bounds__(F8_NTHR, 1) void attn_fp8_kernel(const AttnArgs a) {
   constexpr int KROW = F8_HD;    // bytes per key row
   constexpr int VROW = F8_BKV;   // bytes per value (dim) row
-  __shared__ __attribute__((aligned(16))) uint8_t sK[2][F8_BKV * KROW];
-  __shared__ __attribute__((aligned(16))) uint8_t sV[2][F8_HD * VROW];
-  __shared__ __attribute__((aligned(16))) uint32_t sKs[2][F8_BKV];     // 4 scale bytes per LDS key row
-  __shared__ __attribute__((aligned(16))) uint8_t sVs[2][2 * F8_HD];    // [key block][dim]
+  constexpr int TILE = F8_BKV * F8_HD;
+  __shared__ __attribute__((aligned(1024))) uint8_t sK[F8_SLOTS * TILE];
+  __shared__ __attribute__((aligned(1024))) uint8_t sV[F8_SLOTS * TILE];
+  __shared__ __attribute__((aligned(256))) uint32_t sKs[F8_SLOTS * F8_BKV];     // 4 scale bytes per LDS key row
+  __shared__ __attribute__((aligned(256))) uint8_t sVs[F8_SLOTS * 2 * F8_HD];   // [key block][dim]
 
   const int pid = blockIdx.x;
   const int xcd = pid % kNumXcd;
@@ -232,16 +257,17 @@ __global__ __launch_bounds__(F8_NTHR, 1) void attn_fp8_kernel(const AttnArgs a) 
   const int h = it / S.n_qtiles;
   const int qt = it - h * S.n_qtiles;
   const int32_t* tl = nullptr;
-  int te = S.n_tiles;
+  int nt = S.n_tiles;
   if (LIST) {
     const int ld = a.blk_ld ? a.blk_ld : S.n_keep;
     tl = a.blocks + S.blk_off + static_cast<int64_t>(it) * ld;
-    te = S.n_keep;
+    nt = S.n_keep;
   }
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, hh = lane >> 5;
+  const int grp = wave >> 2;   // waves w and w + 4 share a SIMD: one of each group
 
   // ---- Q fragments (B operand of S^T = K Q^T) and their scales
   i32x8 qf[2];
@@ -262,23 +288,62 @@ __global__ __launch_bounds__(F8_NTHR, 1) void attn_fp8_kernel(const AttnArgs a) 
     }
   }
 
-  // ---- staging: one 16-byte chunk of keys and one of values per thread
+  // ---- staging by direct loads: per wave 1 KB of keys (8 rows; lane i slot i % 8
+  // of row i / 8) and 1 KB of values (16 dims; slot i % 4 of dim i / 4), and one
+  // wave each for the 256 bytes of key and of value scales
   const int pad = F8_BKV * S.n_tiles;
   const size_t head0 = static_cast<size_t>(a.H) * S.base_off + static_cast<size_t>(h) * pad;
-  const uint8_t* kg = a.k8 + head0 * F8_HD;
-  const uint8_t* ksg = a.k8s + head0 * (F8_HD / 32);
-  const uint8_t* vg = a.v8 + head0 * F8_HD;
-  const uint8_t* vsg = a.v8s + (head0 / 32) * F8_HD;
-  const int kr = tid >> 3, kc = tid & 7;
-  const int kR = f8_lds_row(kr);
-  const int k_lds = kR * KROW + ((kc ^ ((kR >> 1) & 7)) << 4);
-  const int vd = tid >> 2, vc = tid & 3;
-  const int v_lds = vd * VROW + ((vc ^ ((vd >> 2) & 3)) << 4);
+  const char* kg = reinterpret_cast<const char*>(a.k8 + head0 * F8_HD);
+  const char* ksg = reinterpret_cast<const char*>(a.k8s + head0 * (F8_HD / 32));
+  const char* vg = reinterpret_cast<const char*>(a.v8 + head0 * F8_HD);
+  const char* vsg = reinterpret_cast<const char*>(a.v8s + (head0 / 32) * F8_HD);
+  const int kR = 8 * wave + (lane >> 3);
+  const uint32_t k_off = static_cast<uint32_t>(f8_row_key(kR) * F8_HD + (((lane & 7) ^ ((kR >> 1) & 7)) << 4));
+  const int vd = 16 * wave + (lane >> 2);
+  const char* v_lane = vg + static_cast<size_t>(vd) * pad + (((lane & 3) ^ ((vd >> 2) & 3)) << 4);
+  const uint32_t ks_off = static_cast<uint32_t>(f8_row_key(lane) * 4), vs_off = static_cast<uint32_t>(lane * 4);
+  const uint32_t lds_k = lds_address(sK) + wave * 1024u, lds_v = lds_address(sV) + wave * 1024u;
+  const uint32_t lds_ks = lds_address(sKs), lds_vs = lds_address(sVs);
   const float c = a.scale_log2;
   const int kv_len = S.kv_len;
 
-  uint4 rk0, rk1, rv0, rv1, rs0, rs1;
-  f32x16 o[4];
+  // lane i: list entry b0 + i, clamped into the stream's tiles
+  auto list_window = [&](int b0) __attribute__((always_inline)) {
+    return min(max(tl[min(b0 + lane, nt - 1)], 0), S.n_tiles - 1);
+  };
+  int lw0 = 0, lw = 0, prev = 0;
+  if (LIST) lw = list_window(0);
+  // Pair u: the keys of position u (u < nt) and the values of position u - 1 (u > 0)
+  auto fetch = [&](int u) __attribute__((always_inline)) {
+    if (u > nt) return;
+    if (u > 0) {
+      const uint32_t sl = static_cast<uint32_t>((u - 1) % F8_SLOTS);
+      lds_dma16(v_lane + F8_BKV * prev, lds_v + sl * TILE);
+      if (wave == 1) lds_dma4(vsg + 2 * F8_HD * static_cast<size_t>(prev), vs_off, lds_vs + sl * (2 * F8_HD));
+    }
+    if (u < nt) {
+      prev = u;
+      if (LIST) {
+        if (u - lw0 >= 64) {
+          lw0 = u;
+          lw = list_window(u);
+          asm volatile("" : "+v"(lw));
+        }
+        prev = __builtin_amdgcn_readlane(lw, u - lw0);
+      }
+      const uint32_t sl = static_cast<uint32_t>(u % F8_SLOTS);
+      lds_dma16(kg + static_cast<size_t>(TILE) * prev, k_off, lds_k + sl * TILE);
+      if (wave == 0) lds_dma4(ksg + 4 * F8_BKV * static_cast<size_t>(prev), ks_off, lds_ks + sl * (4 * F8_BKV));
+    }
+  };
+  // all but the last `pairs` pairs requested by this wave have landed
+  auto wait_pairs = [&](auto pairs_c) __attribute__((always_inline)) {
+    constexpr int P = decltype(pairs_c)::value;
+    if (wave < 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * P) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * P) : "memory");
+  };
+
+  f32x16 o[4], s[2];
 #pragma unroll
   for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -286,88 +351,15 @@ __global__ __launch_bounds__(F8_NTHR, 1) void attn_fp8_kernel(const AttnArgs a) 
   float m_run = -INFINITY;
   float l_run = 0.f;
 
-#define F8_TIX(t) (LIST ? min(max(tl[(t)], 0), S.n_tiles - 1) : (t))
-#define F8_LOAD(tile, SET)                                                                     \
-  {                                                                                            \
-    const int t_ = (tile);                                                                     \
-    rk##SET = *reinterpret_cast<const uint4*>(kg + static_cast<size_t>(F8_BKV * t_ + kr) * F8_HD + 16 * kc); \
-    rv##SET = *reinterpret_cast<const uint4*>(vg + static_cast<size_t>(vd) * pad + F8_BKV * t_ + 16 * vc);  \
-    if (tid < 16)                                                                              \
-      rs##SET = *reinterpret_cast<const uint4*>(ksg + static_cast<size_t>(F8_BKV * t_) * 4 + 16 * tid);     \
-    else if (tid < 32)                                                                         \
-      rs##SET = *reinterpret_cast<const uint4*>(vsg + static_cast<size_t>(2 * t_) * F8_HD + 16 * (tid - 16)); \
-  }
-#define F8_STORE(BUF, SET)                                                                     \
-  {                                                                                            \
-    *reinterpret_cast<uint4*>(&sK[BUF][k_lds]) = rk##SET;                                      \
-    *reinterpret_cast<uint4*>(&sV[BUF][v_lds]) = rv##SET;                                      \
-    if (tid < 16) {                                                                            \
-      sKs[BUF][f8_lds_row(4 * tid)] = rs##SET.x;                                               \
-      sKs[BUF][f8_lds_row(4 * tid + 1)] = rs##SET.y;                                           \
-      sKs[BUF][f8_lds_row(4 * tid + 2)] = rs##SET.z;                                           \
-      sKs[BUF][f8_lds_row(4 * tid + 3)] = rs##SET.w;                                           \
-    } else if (tid < 32) {                                                                     \
-      *reinterpret_cast<uint4*>(&sVs[BUF][16 * (tid - 16)]) = rs##SET;                         \
-    }                                                                                          \
-  }
-
-  // one 64-key tile from LDS buffer buf: scores, online softmax, P in E4M3, PV
-  auto tile_step = [&](const int t, const int buf) {
-    // ---- S^T = K Q^T: two 32-key blocks, two 64-dim steps
-    // all K fragments read first (two 16-byte halves each), then the four MFMAs
-    i32x8 kf[2][2];
-    uint32_t ksc[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      const int R = 32 * kb + n;
-      ksc[kb] = sKs[buf][R];
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const int c0 = 4 * ks + hh, c1 = 4 * ks + 2 + hh;
-        const i32x4 a0 = *reinterpret_cast<const i32x4*>(&sK[buf][R * KROW + ((c0 ^ ((R >> 1) & 7)) << 4)]);
-        const i32x4 a1 = *reinterpret_cast<const i32x4*>(&sK[buf][R * KROW + ((c1 ^ ((R >> 1) & 7)) << 4)]);
-        kf[kb][ks] = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
-      }
-    }
-    f32x16 s[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const int sa = static_cast<int>((ksc[kb] >> (8 * (2 * ks + hh))) & 0xffu);
-        s[kb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kf[kb][ks], qf[ks], s[kb], 0, 0, 0, sa,
-                                                                0, qsc[ks]);
-      }
-    }
-    // V fragments for the PV product, read now so the softmax hides their latency
-    i32x8 vf[4];
-    int vsc[4];
-#pragma unroll
-    for (int db = 0; db < 4; ++db) {
-      const int R = 32 * db + n;
-      const int c0 = hh, c1 = 2 + hh;
-      const i32x4 v0 = *reinterpret_cast<const i32x4*>(&sV[buf][R * VROW + ((c0 ^ ((R >> 2) & 3)) << 4)]);
-      const i32x4 v1 = *reinterpret_cast<const i32x4*>(&sV[buf][R * VROW + ((c1 ^ ((R >> 2) & 3)) << 4)]);
-      vf[db] = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
-      vsc[db] = sVs[buf][hh * F8_HD + R];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    const int tile = F8_TIX(t);
-    if (F8_BKV * tile + F8_BKV > kv_len) {   // keys past the end (last tile only)
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (F8_BKV * tile + 32 * kb + 16 * hh + i >= kv_len) s[kb][i] = -INFINITY;
-    }
-    // ---- online softmax (scaled log2 units, lazy rescale by more than 2^8).
-    // Each 32-key block's largest score gives its largest weight (exp2 is
-    // monotonic), hence the block's E4M3 exponent before any weight exists;
-    // the exponent is folded into the exp2 argument, so the weights come out
-    // already divided by their block scale.
-    float sb0 = -INFINITY, sb1 = -INFINITY;
+  // MFMA phase of position t: S^T = K Q^T of position t (two 32-key blocks, two
+  // 64-dim steps) beside the conversion of the weights of position t - 1, then
+  // O^T += V^T P^T of position t - 1 (four 32-dim blocks) beside the block
+  // maxima of position t
+  f32x16 p[2];              // weights of the last VALU phase, scaled by their blocks
+  int e0 = 0, e1 = 0;       // their exponents
+  float sb0 = 0.f, sb1 = 0.f;   // largest score of each block (over the block's lane pair)
+  auto block_max = [&]() __attribute__((always_inline)) {
+    sb0 = sb1 = -INFINITY;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       sb0 = fmaxf(sb0, s[0][i]);
@@ -375,6 +367,93 @@ __global__ __launch_bounds__(F8_NTHR, 1) void attn_fp8_kernel(const AttnArgs a) 
     }
     sb0 = half_pair_max(sb0);
     sb1 = half_pair_max(sb1);
+  };
+  auto mfma_phase = [&](int t, auto pv_c) __attribute__((always_inline)) {
+    constexpr bool PV = decltype(pv_c)::value;
+    __builtin_amdgcn_s_setprio(1);
+    i32x8 vf[4], kf[2][2], pf;
+    int vsc[4];
+    uint32_t ksc[2];
+    const uint8_t* tk = &sK[(t % F8_SLOTS) * TILE];
+    const uint32_t* tks = &sKs[(t % F8_SLOTS) * F8_BKV];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      const int R = 32 * kb + n;
+      ksc[kb] = tks[R];
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const int c0 = 4 * ks + hh, c1 = 4 * ks + 2 + hh;
+        const i32x4 a0 = *reinterpret_cast<const i32x4*>(&tk[R * KROW + ((c0 ^ ((R >> 1) & 7)) << 4)]);
+        const i32x4 a1 = *reinterpret_cast<const i32x4*>(&tk[R * KROW + ((c1 ^ ((R >> 1) & 7)) << 4)]);
+        kf[kb][ks] = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
+      }
+    }
+    if constexpr (PV) {
+      const uint8_t* tv = &sV[((t - 1) % F8_SLOTS) * TILE];
+      const uint8_t* tvs = &sVs[((t - 1) % F8_SLOTS) * 2 * F8_HD];
+#pragma unroll
+      for (int db = 0; db < 4; ++db) {
+        const int R = 32 * db + n;
+        const int c0 = hh, c1 = 2 + hh;
+        const i32x4 v0 = *reinterpret_cast<const i32x4*>(&tv[R * VROW + ((c0 ^ ((R >> 2) & 3)) << 4)]);
+        const i32x4 v1 = *reinterpret_cast<const i32x4*>(&tv[R * VROW + ((c1 ^ ((R >> 2) & 3)) << 4)]);
+        vf[db] = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+        vsc[db] = tvs[hh * F8_HD + R];
+      }
+    }
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        const int sa = static_cast<int>((ksc[kb] >> (8 * (2 * ks + hh))) & 0xffu);
+        s[kb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kf[kb][ks], qf[ks], s[kb], 0, 0, 0, sa, 0, qsc[ks]);
+      }
+    if constexpr (PV) {
+      // P in E4M3, one scale per 32-key block (this lane supplies block hh's),
+      // and the block sums of the unquantised weights
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        pf[w] = static_cast<int>(pack4_e4m3(p[0][4 * w], p[0][4 * w + 1], p[0][4 * w + 2], p[0][4 * w + 3]));
+        pf[4 + w] = static_cast<int>(pack4_e4m3(p[1][4 * w], p[1][4 * w + 1], p[1][4 * w + 2], p[1][4 * w + 3]));
+      }
+      float ps0 = 0.f, ps1 = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        ps0 += p[0][i];
+        ps1 += p[1][i];
+      }
+      l_run = fmaf(ps0, __uint_as_float(static_cast<uint32_t>(127 + e0) << 23),
+                   fmaf(ps1, __uint_as_float(static_cast<uint32_t>(127 + e1) << 23), l_run));
+      const int psc = (hh ? e1 : e0) + 127;
+#pragma unroll
+      for (int db = 0; db < 4; ++db)
+        o[db] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vf[db], pf, o[db], 0, 0, 0, vsc[db], 0, psc);
+    }
+    block_max();
+    asm volatile("" : "+v"(sb0), "+v"(sb1), "+v"(l_run));
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  // VALU phase: online softmax of the scores into p
+  auto softmax = [&](const bool ends, const int tile) __attribute__((always_inline)) {
+    if (ends && F8_BKV * tile + F8_BKV > kv_len) {   // keys past the end (the last position only)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (F8_BKV * tile + 32 * kb + 16 * hh + i >= kv_len) s[kb][i] = -INFINITY;
+      block_max();
+    }
+    // online softmax (scaled log2 units, lazy rescale by more than 2^8).
+    // Each 32-key block's largest score gives its largest weight (exp2 is
+    // monotonic), hence the block's E4M3 exponent before any weight exists;
+    // the exponent is folded into the exp2 argument, so the weights come out
+    // already divided by their block scale.
     const float mx = fmaxf(sb0, sb1) * c;
     if (__any(mx > m_run + 8.0f)) {
       const float m_new = fmaxf(m_run, mx);
@@ -386,60 +465,62 @@ __global__ __launch_bounds__(F8_NTHR, 1) void attn_fp8_kernel(const AttnArgs a) 
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
     }
-    const int e0 = mx_exponent_nb(__builtin_amdgcn_exp2f(fmaf(sb0, c, -m_run)));
-    const int e1 = mx_exponent_nb(__builtin_amdgcn_exp2f(fmaf(sb1, c, -m_run)));
+    e0 = mx_exponent_nb(__builtin_amdgcn_exp2f(fmaf(sb0, c, -m_run)));
+    e1 = mx_exponent_nb(__builtin_amdgcn_exp2f(fmaf(sb1, c, -m_run)));
     const float m0 = m_run + static_cast<float>(e0), m1 = m_run + static_cast<float>(e1);
-    float ps0 = 0.f, ps1 = 0.f;   // block sums of the scaled weights
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const float p0 = __builtin_amdgcn_exp2f(fmaf(s[0][i], c, -m0));
-      const float p1 = __builtin_amdgcn_exp2f(fmaf(s[1][i], c, -m1));
-      s[0][i] = p0;
-      s[1][i] = p1;
-      ps0 += p0;
-      ps1 += p1;
+      p[0][i] = __builtin_amdgcn_exp2f(fmaf(s[0][i], c, -m0));
+      p[1][i] = __builtin_amdgcn_exp2f(fmaf(s[1][i], c, -m1));
     }
-    l_run = fmaf(ps0, __uint_as_float(static_cast<uint32_t>(127 + e0) << 23),
-                 fmaf(ps1, __uint_as_float(static_cast<uint32_t>(127 + e1) << 23), l_run));
-    // ---- P in E4M3, one scale per 32-key block (this lane supplies block hh's)
-    i32x8 pf;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      pf[w] = static_cast<int>(pack4_e4m3(s[0][4 * w], s[0][4 * w + 1], s[0][4 * w + 2], s[0][4 * w + 3]));
-      pf[4 + w] = static_cast<int>(pack4_e4m3(s[1][4 * w], s[1][4 * w + 1], s[1][4 * w + 2], s[1][4 * w + 3]));
-    }
-    const int psc = (hh ? e1 : e0) + 127;
-    // ---- O^T += V^T P^T: four 32-dim blocks
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-      o[db] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vf[db], pf, o[db], 0, 0, 0, vsc[db], 0,
-                                                              psc);
+    // formed here, in this phase
+    asm volatile("" : "+v"(p[0]), "+v"(p[1]), "+v"(e0), "+v"(e1));
   };
+  const std::true_type yes;
+  const std::false_type no;
+  const std::integral_constant<int, 0> w0;
+  const std::integral_constant<int, 2> w2;
+  const std::integral_constant<int, 3> w3;
 
-  // two tiles of loads in flight: register set t & 1 holds tile t until stored
-  F8_LOAD(F8_TIX(0), 0);
-  if (1 < te) F8_LOAD(F8_TIX(1), 1);
-  F8_STORE(0, 0);
+  // ---- prologue: the pairs ahead of the group's first VALU phase
+#pragma unroll 1
+  for (int u = 0; u < 3 + grp; ++u) fetch(u);
+  const bool lead = 3 + grp < nt;   // the pairs after pair 0 are whole
+  if (!lead) wait_pairs(w0);
+  else if (grp == 0) wait_pairs(w2);
+  else wait_pairs(w3);
   __syncthreads();
-  for (int t0 = 0; t0 < te; t0 += 2) {
-    {
-      const int t = t0;
-      if (t + 2 < te) F8_LOAD(F8_TIX(t + 2), 0);
-      tile_step(t, 0);
-      if (t + 1 < te) F8_STORE(1, 1);
-      __syncthreads();
+  const int last_tile = LIST ? min(max(tl[nt - 1], 0), S.n_tiles - 1) : nt - 1;
+  // the pair read after the next barrier has landed; `u` is the last pair requested
+  auto wait_next = [&](int u) __attribute__((always_inline)) {
+    if (u < nt) wait_pairs(w2);
+    else wait_pairs(w0);
+  };
+  if (qt * F8_BQ + wave * 32 < S.q_len) {
+    mfma_phase(0, no);
+#pragma unroll 1
+    for (int t = 0; t < nt; ++t) {
+      if (grp == 1) {
+        wait_next(t + 3);
+        __syncthreads();
+      }
+      fetch(t + 3 + grp);
+      softmax(t == nt - 1, last_tile);
+      if (grp == 0) {
+        wait_next(t + 3);
+        __syncthreads();
+      }
+      mfma_phase(t + 1, yes);   // (past the last position the scores are not used)
     }
-    if (t0 + 1 < te) {
-      const int t = t0 + 1;
-      if (t + 2 < te) F8_LOAD(F8_TIX(t + 2), 1);
-      tile_step(t, 1);
-      if (t + 1 < te) F8_STORE(0, 0);
+  } else {   // no query of this wave exists: it only stages
+#pragma unroll 1
+    for (int t = 0; t < nt; ++t) {
+      if (grp == 0) fetch(t + 3);
+      wait_next(t + 3);
       __syncthreads();
+      if (grp == 1) fetch(t + 4);
     }
   }
-#undef F8_LOAD
-#undef F8_STORE
-#undef F8_TIX
   // ---- normalised bf16 output: lane holds dims 32 db + 8 g + 4 hh + 0..3 of its query
   const auto lp = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run),
                                                     false, false);

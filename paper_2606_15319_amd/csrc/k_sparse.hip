@@ -370,7 +370,14 @@ hipError_t launch_sparse_select(hipStream_t st, const AttnArgs& a, int head_dim)
   int max_tiles = 0;
   for (int i = 0; i < a.n_streams; ++i)
     if (a.s[i].n_keep < a.s[i].n_tiles) max_tiles = max(max_tiles, a.s[i].n_tiles);
-  if (max_tiles <= 64 * 16) {
+  // the search counts every register of the wave in each of its 32 steps, so the
+  // register count follows the longest stream (512 tiles: 11.5 us with 16 registers
+  // a lane, 8.4 with 8)
+  if (max_tiles <= 64 * 4) {
+    hipLaunchKernelGGL(select_kernel<4>, g_item, dim3(64), 0, st, a);
+  } else if (max_tiles <= 64 * 8) {
+    hipLaunchKernelGGL(select_kernel<8>, g_item, dim3(64), 0, st, a);
+  } else if (max_tiles <= 64 * 16) {
     hipLaunchKernelGGL(select_kernel<16>, g_item, dim3(64), 0, st, a);
   } else {
     const size_t lds = sizeof(uint32_t) * 64 * ((max_tiles + 63) / 64);

@@ -603,12 +603,13 @@ __global__ __launch_bounds__(NTHR, 1) void attn_split_kernel(const AttnArgs a) {
   const int pid = blockIdx.x;
   const int xcd = pid % kNumXcd, j = pid / kNumXcd;
 
-  // XCD x runs items [pre, pre + nx), then its share of the tail ranges
-  const int ipx = a.total_items / kNumXcd, irem = a.total_items % kNumXcd;
+  // XCD x runs items item0 + [pre, pre + nx), then its share of the tail ranges
+  const int items = a.total_items - a.item0;
+  const int ipx = items / kNumXcd, irem = items % kNumXcd;
   const int nx = ipx + (xcd < irem ? 1 : 0);
   const int pre = xcd * ipx + min(xcd, irem);
   if (j < nx) {
-    const int gi = pre + j;
+    const int gi = a.item0 + pre + j;
     int si = 0;
     for (int i = 1; i < a.n_streams; ++i)
       if (gi >= a.s[i].item_begin) si = i;
@@ -616,11 +617,11 @@ __global__ __launch_bounds__(NTHR, 1) void attn_split_kernel(const AttnArgs a) {
     const int item = gi - S.item_begin;
     const int h = item / S.n_qtiles, qt = item - h * S.n_qtiles;
     attn_range<HD, PAGED, VEC>(a, S, h, qt, 0, S.main_tiles, sK, sV,
-                               S.main_tiles == S.n_tiles ? -1 : gi);
+                               S.main_tiles == S.n_tiles ? -1 : gi - a.item0);
     return;
   }
   const int r = a.per_xcd * xcd + j - (pre + nx);   // tail range
-  if (r >= a.split_blocks - a.total_items) return;
+  if (r >= a.split_blocks - items) return;
   int pos = r * a.split_tiles;
   const int end = min(pos + a.split_tiles, a.total_tiles);
   while (pos < end) {
@@ -630,15 +631,16 @@ __global__ __launch_bounds__(NTHR, 1) void attn_split_kernel(const AttnArgs a) {
     const AttnStream S = a.s[si];
     const int tl = S.n_tiles - S.main_tiles;
     const int rel = pos - S.tail_begin;
-    const int item = rel / tl;
-    const int tb = S.main_tiles + (rel - item * tl);
+    const int first = max(0, a.item0 - S.item_begin);   // the stream's first item of this schedule
+    const int item = first + rel / tl;
+    const int tb = S.main_tiles + rel % tl;
     const int te = min(S.n_tiles, tb + (end - pos));
     pos += te - tb;
     const int h = item / S.n_qtiles, qt = item - h * S.n_qtiles;
-    // piece (range r, item i) -> slot total_items + i + r: items increase within a
+    // piece (range r, item i) -> slot items + i + r: items increase within a
     // range and the next range starts at the last one's last item, so slots differ
     attn_range<HD, PAGED, VEC>(a, S, h, qt, tb, te, sK, sV,
-                               static_cast<int64_t>(a.total_items) + S.item_begin + item + r);
+                               static_cast<int64_t>(items) + S.item_begin + item - a.item0 + r);
   }
 }
 
@@ -646,12 +648,12 @@ __global__ __launch_bounds__(NTHR, 1) void attn_split_kernel(const AttnArgs a) {
 // o = sum_j 2^(m_j - M) O_j / sum_j 2^(m_j - M) l_j, M = max_j m_j, over the
 // item's main part (slot = item) and the pieces of its tail [w0, w1) of the
 // concatenated tails, held by ranges w0 / W .. (w1 - 1) / W (slot
-// total_items + item + range).
+// items + item + range, items counted from item0).
 template <int HD>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const AttnArgs a) {
   constexpr int TPR = HD / 4;          // threads per row, 4 dims each
   constexpr int RPB = 256 / TPR;       // rows per workgroup
-  const int gi = blockIdx.x / (BQ / RPB);
+  const int gi = a.item0 + blockIdx.x / (BQ / RPB);
   const int row = (blockIdx.x % (BQ / RPB)) * RPB + threadIdx.x / TPR;
   int si = 0;
   for (int i = 1; i < a.n_streams; ++i)
@@ -660,7 +662,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const AttnArgs a) {
   const int item = gi - S.item_begin;
   const int tl = S.n_tiles - S.main_tiles;
   if (tl == 0) return;   // written whole by its main part
-  const int w0 = S.tail_begin + item * tl, w1 = w0 + tl;
+  const int w0 = S.tail_begin + (item - max(0, a.item0 - S.item_begin)) * tl, w1 = w0 + tl;
+  const int li = gi - a.item0, items = a.total_items - a.item0;
   const int W = a.split_tiles;
   const int b_lo = w0 / W, b_hi = (w1 - 1) / W;
   const int h = item / S.n_qtiles;
@@ -669,15 +672,15 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const AttnArgs a) {
   const int ql = qt * BQ + row;
   if (ql >= S.q_len) return;
   {
-    float M = a.part_ml[static_cast<size_t>(gi) * 2 * BQ + row];
+    float M = a.part_ml[static_cast<size_t>(li) * 2 * BQ + row];
     for (int b = b_lo; b <= b_hi; ++b) {
-      const size_t slot = static_cast<size_t>(a.total_items) + gi + b;
+      const size_t slot = static_cast<size_t>(items) + li + b;
       M = fmaxf(M, a.part_ml[slot * 2 * BQ + row]);
     }
     float l = 0.f;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int b = b_lo - 1; b <= b_hi; ++b) {
-      const size_t slot = b < b_lo ? static_cast<size_t>(gi) : static_cast<size_t>(a.total_items) + gi + b;
+      const size_t slot = b < b_lo ? static_cast<size_t>(li) : static_cast<size_t>(items) + li + b;
       const float wgt = __builtin_amdgcn_exp2f(a.part_ml[slot * 2 * BQ + row] - M);
       l += wgt * a.part_ml[slot * 2 * BQ + BQ + row];
       const float4 p = *reinterpret_cast<const float4*>(a.part_o + (slot * BQ + row) * HD + 4 * d4);
@@ -1090,6 +1093,7 @@ void plan_attention(AttnArgs& a, int head_dim, float* split_ws) {
   a.n_streams = n;
   a.total_items = items;
   a.small = 0;
+  a.item0 = 0;
   a.total_tiles = 0;
   a.split_blocks = 0;
   a.split_tiles = 0;
@@ -1127,26 +1131,52 @@ void plan_attention(AttnArgs& a, int head_dim, float* split_ws) {
   // of the remaining tails.  Items of one head still run their main parts in
   // step, sharing key tiles through L2.  The tail ranges cost more per tile
   // (short segments, partial writes, the merge), which outweighs the gain when
-  // few workgroups are idle.  The round is cut to as many workgroups as have
+  // few workgroups are idle (228 items of 220 tiles, 28 workgroups idle: 426 us split,
+  // 352 whole).  The round is cut to as many workgroups as have
   // eight tiles each (a multiple of the XCDs; 1440 queries over 4320 keys, 4 heads
   // of 64, 1632 tiles on 24 items: 92 us unsplit, 34 on 200 workgroups).
+  //
+  // Items of equal cost that fill one to three rounds and leave more than a
+  // quarter of the last one idle run their full rounds whole and split the rest
+  // the same way in a second launch: 380 items of 585 tiles (4680 queries over
+  // 37440 keys, 20 heads) 1520 us for 1770.  The launch and the merge take
+  // about 20 us, so the idle share has to be worth 24 tiles of the round; with
+  // more rounds, or with mixed costs (where shorter items fill the gaps), it is
+  // not.
+  const bool uniform = n > 0 && tmp[0].n_tiles == tmp[n - 1].n_tiles;   // (ordered by cost)
+  int item0 = 0;
+  if (items > kAttnSplitBlocks) {
+    const int rem = items % kAttnSplitBlocks;
+    const int idle = kAttnSplitBlocks - rem;
+    if (!uniform || rem == 0 || items > 4 * kAttnSplitBlocks ||
+        static_cast<int64_t>(idle) * tmp[0].n_tiles < 24 * kAttnSplitBlocks)
+      item0 = items;
+    else
+      item0 = items - rem;
+    work = item0 < items ? static_cast<int64_t>(rem) * tmp[0].n_tiles : 0;
+  }
+  const int left = items - item0;   // items to split
   const int blocks = static_cast<int>(min(static_cast<int64_t>(kAttnSplitBlocks), work / 8 / kNumXcd * kNumXcd));
-  const int spare = blocks - items;
-  if (split_ws && items > 0 && spare * 4 > blocks && work < (static_cast<int64_t>(1) << 30)) {
+  const int spare = blocks - left;
+  if (split_ws && left > 0 && spare * 4 > blocks && work < (static_cast<int64_t>(1) << 30)) {
     const int W = static_cast<int>((work + blocks - 1) / blocks);
     int64_t tails = 0;
     for (int i = 0; i < n; ++i) {
       tmp[i].main_tiles = min(tmp[i].n_tiles, W);
       tmp[i].tail_begin = static_cast<int32_t>(tails);
-      tails += static_cast<int64_t>(tmp[i].n_qtiles) * a.H * (tmp[i].n_tiles - tmp[i].main_tiles);
+      const int here = tmp[i].n_qtiles * a.H - min(tmp[i].n_qtiles * a.H, max(0, item0 - tmp[i].item_begin));
+      tails += static_cast<int64_t>(here) * (tmp[i].n_tiles - tmp[i].main_tiles);
     }
     if (tails > 0) {
+      a.item0 = item0;
       a.split_blocks = blocks;
       a.total_tiles = static_cast<int32_t>(tails);
       a.split_tiles = static_cast<int32_t>((tails + spare - 1) / spare);
       a.part_o = split_ws;
       a.part_ml = split_ws + static_cast<size_t>(2) * kAttnSplitBlocks * BQ * head_dim;
       a.per_xcd = blocks / kNumXcd;
+      // the full rounds: a whole number of items per XCD
+      for (int x = 0; x <= kNumXcd; ++x) a.xcd_begin[x] = item0 / kNumXcd * x;
     } else {
       for (int i = 0; i < n; ++i) tmp[i].main_tiles = tmp[i].n_tiles;
     }
@@ -1160,9 +1190,11 @@ static void launch_attn_t(hipStream_t st, const AttnArgs& a, dim3 grid) {
   if (a.small) {
     hipLaunchKernelGGL((attn_small_kernel<HD, P, V>), grid, dim3(64 * SM_WAVES), 0, st, a);
   } else if (a.split_blocks) {
+    if (a.item0 > 0)
+      hipLaunchKernelGGL((attn_kernel<HD, P, V>), dim3(a.item0), dim3(NTHR), 0, st, a);
     hipLaunchKernelGGL((attn_split_kernel<HD, P, V>), grid, dim3(NTHR), 0, st, a);
-    hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3(a.total_items * (BQ / (256 / (HD / 4)))),
-                       dim3(256), 0, st, a);
+    hipLaunchKernelGGL((attn_merge_kernel<HD>),
+                       dim3((a.total_items - a.item0) * (BQ / (256 / (HD / 4)))), dim3(256), 0, st, a);
   } else {
     hipLaunchKernelGGL((attn_kernel<HD, P, V>), grid, dim3(NTHR), 0, st, a);
   }

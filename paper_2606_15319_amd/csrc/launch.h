@@ -82,6 +82,7 @@ struct AttnArgs {
                                    // [xcd_begin[x], xcd_begin[x + 1]), in order
   int32_t small;         // items of 32 queries, the keys split between a workgroup's waves
   int32_t split_blocks;  // 0: one workgroup per item; else the workgroups of a split schedule
+  int32_t item0;         // split: items before item0 run whole, in full rounds
   int32_t total_tiles;   // split: tail tiles of all items, concatenated
   int32_t split_tiles;   // split: tail tiles per spare workgroup
   float* part_o;         // [2 split_blocks][256][d] partial unnormalised outputs

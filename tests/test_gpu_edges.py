@@ -185,3 +185,23 @@ def test_attn_sparse_few_tiles(A, quant, keys):
     else:
         ref = SR.sparse_attention(qs[0], ks[0], vs[0], lists)
         parity(got, ref, f"keys {keys}", quantum=ref)
+
+
+@pytest.mark.parametrize("q_lens", [[3328, 3328], [2500, 4096], [3072, 3500]])
+def test_attn_full_rounds_and_split_rest(A, q_lens):
+    """260 to 280 items of 10 heads.  Two streams of 52 tiles fill one round whole
+    and split its last four items, which lie in the second stream; streams of
+    different length (40 and 64 tiles, 48 and 55) run one workgroup per item."""
+    from harness import parity
+    from test_gpu_parity import _attn, _attn_case
+    sh = BlockShape(dim=640, n_heads=10, head_dim=64, ffn_dim=512, frames=1, lat_h=8, lat_w=8)
+    pc, dims, batch, q, o, qs, ks, vs = _attn_case(A, sh, q_lens, [0, 0], 440)
+    _attn(A, dims, batch, q, pc.kv(A), o)
+    _sync()
+    og, off = host_f32(o), 0
+    for b, n in enumerate(q_lens):
+        got = og[off:off + n].reshape(n, 10, 64)
+        for h in (0, 5, 9):
+            ref = O.attention(qs[b][:, h:h + 1], ks[b][:, h:h + 1], vs[b][:, h:h + 1])
+            parity(got[:, h:h + 1], ref, f"stream {b} head {h}", quantum=ref)
+        off += n

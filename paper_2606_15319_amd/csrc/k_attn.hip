@@ -27,7 +27,10 @@
 // a quarter of the CUs idle, each item keeps the first part of its key range
 // and the idle workgroups share the remaining parts; the pieces leave partial
 // results (unnormalised O, running max and denominator in fp32) that a second
-// kernel merges.
+// kernel merges.  A last round of items that leaves as many idle is cut the same
+// way after the full rounds (plan_attention).  Calls of few queries over few keys
+// take workgroups of 32 queries that split the keys between their waves
+// (attn_small_kernel).
 #include <math.h>
 #include <string.h>
 

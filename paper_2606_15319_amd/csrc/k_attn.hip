@@ -356,6 +356,11 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
   // range's ends the last tile, when keys run out inside it, and text of odd
   // length go through registers, zeroed past the end.  (Lane indices are taken
   // anew there: shared with the main loop they would stay in registers across it.)
+  // A list's items have few tiles, so there the partial tile takes one trip to
+  // memory, from the bases at hand: 11 kept tiles 38.7 -> 36.7 us, 52 of 512 with the
+  // selection 139.5 -> 136.6.  Over all tiles the trips hide (2 us of an item's 340),
+  // and the same code there cost the main loop 1% (37440 keys of 20 heads 1498 ->
+  // 1526 us, the large block 5703 -> 5780: other registers).
   auto fetch = [&](int u) __attribute__((always_inline)) {
     if (u > 0 && u <= n) {
       const int t = id;   // pairs are fetched in order: the tile of the keys before
@@ -364,17 +369,39 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
       } else {
         int ln = threadIdx.x & 63;
         asm volatile("" : "+v"(ln));
-        const TileMap m = map_tile<HD, PAGED>(a, S, h, t * BKV);
         const int dim = 8 * wave + (ln >> 3), key = 8 * ((ln & 7) ^ swz<BKV * 2>(dim));
-        const int o_ = m.off0 + key;
-        const bf16_t* vb = (o_ < m.T ? m.v0 + o_ : m.v1 + (o_ - m.T)) + static_cast<size_t>(dim) * vstride;
         const int left = kv_len - t * BKV - key;
         bf16_t* dst = &sV[((u - 1) % NSLOT) * TILE + wave * 512 + ln * 8];
+        if constexpr (LIST) {
+          static_assert(VEC && PAGED, "lists are of paged tiles");
+          // t's bases are still at hand (move_to(u) comes after).  Pieces of 8 keys are
+          // 16-byte aligned, and one that holds a key lies whole in its page's row.
+          const int o_ = off0 + key;
+          const bf16_t* vb = reinterpret_cast<const bf16_t*>(o_ >= a.T ? vp1 : vp0) + o_ +
+                             static_cast<size_t>(dim) * vstride;
+          u32x4 x[NI];
+#pragma unroll
+          for (int j = 0; j < NI; ++j) {
+            x[j] = u32x4{0u, 0u, 0u, 0u};
+            if (left > 0) x[j] = *reinterpret_cast<const u32x4*>(vb + static_cast<size_t>(64 * j) * vstride);
+          }
+#pragma unroll
+          for (int j = 0; j < NI; ++j) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)   // (past the end the page may hold anything)
+              x[j][i] = 2 * i + 1 < left ? x[j][i] : (2 * i < left ? x[j][i] & 0xffffu : 0u);
+            *reinterpret_cast<u32x4*>(dst + j * 4096) = x[j];
+          }
+        } else {
+          const TileMap m = map_tile<HD, PAGED>(a, S, h, t * BKV);
+          const int o_ = m.off0 + key;
+          const bf16_t* vb = (o_ < m.T ? m.v0 + o_ : m.v1 + (o_ - m.T)) + static_cast<size_t>(dim) * vstride;
 #pragma unroll 1
-        for (int j = 0; j < NI; ++j)
+          for (int j = 0; j < NI; ++j)
 #pragma unroll 1
-          for (int e = 0; e < 8; ++e)
-            dst[j * 4096 + e] = e < left ? vb[static_cast<size_t>(64 * j) * vstride + e] : bf16_t(0);
+            for (int e = 0; e < 8; ++e)
+              dst[j * 4096 + e] = e < left ? vb[static_cast<size_t>(64 * j) * vstride + e] : bf16_t(0);
+        }
       }
     }
     if (u < n) {
@@ -385,16 +412,32 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
       } else {   // (a partial tile's values come with the next pair, through registers)
         int ln = threadIdx.x & 63;
         asm volatile("" : "+v"(ln));
-        const TileMap m = map_tile<HD, PAGED>(a, S, h, t * BKV);
+        if constexpr (LIST) {
+          u32x4 x[NI];
+#pragma unroll
+          for (int j = 0; j < NI; ++j) {
+            const int R = (wave * NI + j) * KROWS + ln / CPR;
+            const int key = kappa16(R >> 4, R & 15), o_ = off0 + key;
+            const bf16_t* b = reinterpret_cast<const bf16_t*>(o_ >= a.T ? kp1 : kp0) +
+                              static_cast<ptrdiff_t>(o_) * HD + 8 * ((ln % CPR) ^ swz<HD * 2>(R & 15));
+            x[j] = u32x4{0u, 0u, 0u, 0u};
+            if (t * BKV + key < kv_len) x[j] = *reinterpret_cast<const u32x4*>(b);
+          }
+#pragma unroll
+          for (int j = 0; j < NI; ++j)
+            *reinterpret_cast<u32x4*>(&sK[(u % NSLOT) * TILE + (wave * NI + j) * 512 + ln * 8]) = x[j];
+        } else {
+          const TileMap m = map_tile<HD, PAGED>(a, S, h, t * BKV);
 #pragma unroll 1
-        for (int j = 0; j < NI; ++j) {
-          const int R = (wave * NI + j) * KROWS + ln / CPR;
-          const int key = kappa16(R >> 4, R & 15), o_ = m.off0 + key;
-          const bf16_t* b = (o_ < m.T ? m.k0 + static_cast<size_t>(o_) * HD : m.k1 + static_cast<size_t>(o_ - m.T) * HD) +
-                            8 * ((ln % CPR) ^ swz<HD * 2>(R & 15));
-          u32x4 x = {0u, 0u, 0u, 0u};
-          if (t * BKV + key < kv_len) x = *reinterpret_cast<const u32x4*>(b);
-          *reinterpret_cast<u32x4*>(&sK[(u % NSLOT) * TILE + (wave * NI + j) * 512 + ln * 8]) = x;
+          for (int j = 0; j < NI; ++j) {
+            const int R = (wave * NI + j) * KROWS + ln / CPR;
+            const int key = kappa16(R >> 4, R & 15), o_ = m.off0 + key;
+            const bf16_t* b = (o_ < m.T ? m.k0 + static_cast<size_t>(o_) * HD : m.k1 + static_cast<size_t>(o_ - m.T) * HD) +
+                              8 * ((ln % CPR) ^ swz<HD * 2>(R & 15));
+            u32x4 x = {0u, 0u, 0u, 0u};
+            if (t * BKV + key < kv_len) x = *reinterpret_cast<const u32x4*>(b);
+            *reinterpret_cast<u32x4*>(&sK[(u % NSLOT) * TILE + (wave * NI + j) * 512 + ln * 8]) = x;
+          }
         }
       }
     }

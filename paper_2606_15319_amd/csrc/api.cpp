@@ -937,9 +937,12 @@ int ardit_ctx_kv(hipStream_t stream, const ardit_dims* dims, const ardit_batch* 
   bf16_t* cv = at<bf16_t>(ws, L.cv);
   const RowStreams rs = ctx_streams(batch);
   auto B16 = [](const void* q) { return static_cast<const bf16_t*>(q); };
+  // values go straight to their place only where no workgroup still reads ctx there
+  const size_t nb = sizeof(bf16_t) * static_cast<size_t>(Nc) * D;
+  bf16_t* v_direct = overlaps(ctx, nb, ctx_v, nb) ? nullptr : static_cast<bf16_t*>(ctx_v);
   bool v_done = false;
   ARDIT_HIP(launch_ctx_gemms(stream, B16(ctx), Nc, D, B16(w->w_ck), B16(w->b_ck), ck, B16(w->w_cv),
-                             B16(w->b_cv), cv, static_cast<bf16_t*>(ctx_v), rs, &v_done),
+                             B16(w->b_cv), cv, v_direct, rs, &v_done),
             "ctx k / v gemm");
   ARDIT_HIP(launch_ctx_k_layout(stream, ck, Nc, D, dims->n_heads, dims->head_dim, B16(w->g_ck),
                                 dims->eps, static_cast<bf16_t*>(ctx_k), rs),

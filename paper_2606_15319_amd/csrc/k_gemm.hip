@@ -622,7 +622,7 @@ hipError_t launch_ctx_gemms(hipStream_t st, const bf16_t* ctx, int M, int D, con
   GemmEpiArgs e;
   e.bias = bk;
   // the tile rule of small_tile on the workgroups of both products
-  const int tile = small_tile(M, 2 * D);
+  const int tile = ctx_v ? small_tile(M, 2 * D) : 0;
   if (tile) {
     SmallDual du{};
     du.W2 = Wv;

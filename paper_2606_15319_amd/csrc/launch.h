@@ -165,7 +165,8 @@ struct RowStreams {
 
 // Text projections of one block in one launch: ck = ctx Wk^T + bk ([M][D]) and
 // the values ctx Wv^T + bv, either straight into ctx_v ([H][hd][len] per stream
-// at element row_begin * D; *v_done true) or as rows into cv ([M][D]).
+// at element row_begin * D; *v_done true) or as rows into cv ([M][D]); ctx_v
+// NULL: rows.
 hipError_t launch_ctx_gemms(hipStream_t st, const bf16_t* ctx, int M, int D, const bf16_t* Wk,
                             const bf16_t* bk, bf16_t* ck, const bf16_t* Wv, const bf16_t* bv,
                             bf16_t* cv, bf16_t* ctx_v, const RowStreams& rs, bool* v_done);

@@ -43,7 +43,7 @@ def test_time_mod_rows_and_stream_groups(A, dim, n):
         assert np.max(np.abs(got[i] - ref)) <= 2e-5 * np.sqrt(np.mean(ref ** 2)), (dim, n, i)
 
 
-def _ctx_case(A, dim, lens, seed):
+def _ctx_case(A, dim, lens, seed, in_place=False):
     import torch
     from harness import upload_block_weights
     from paper_2606_15319_amd.layout import ctx_from_device_layout
@@ -54,12 +54,12 @@ def _ctx_case(A, dim, lens, seed):
     rng = make_rng(seed + 1)
     ctx = [normal_bf16(rng, (n, dim)) for n in lens]
     dims, batch = A.dims_from_shape(sh), A.Batch(ctx_lens=lens)
+    src = dev_bf16(np.concatenate(ctx))
     ck = torch.full((sum(lens) * dim,), float("nan"), dtype=torch.bfloat16, device="cuda")
-    cv = torch.full_like(ck, float("nan"))
+    cv = src.view(-1) if in_place else torch.full_like(ck, float("nan"))
     n = A.ardit_workspace_size(dims, batch)
     ws = torch.empty(n, dtype=torch.uint8, device="cuda")
-    A.ardit_ctx_kv(None, dims, batch, dev_bf16(np.concatenate(ctx)), A.block_weights(upload_block_weights(w)),
-                   ck, cv, ws, n)
+    A.ardit_ctx_kv(None, dims, batch, src, A.block_weights(upload_block_weights(w)), ck, cv, ws, n)
     _sync()
     kf, vf, off, out = host_f32(ck), host_f32(cv), 0, []
     for b, m in enumerate(lens):
@@ -75,12 +75,21 @@ def _ctx_case(A, dim, lens, seed):
     (384, [512, 77]),       # six K steps (the ring wraps once), the last row tile half full
     (1536, [512, 77]),      # 64-row tiles
     (1536, [700, 500]),     # the large tiles, both products in one launch, values transposed after
+    (1152, [900, 700]),     # the same, each product's last column tile half full
 ])
 def test_ctx_kv_tiles(A, dim, lens):
     from harness import parity
     for b, (k, v, kr, vr) in enumerate(_ctx_case(A, dim, lens, 410)):
         parity(k, kr, f"k {dim} {b}", quantum=kr)
         parity(v, vr, f"v {dim} {b}", quantum=vr)
+
+
+def test_ctx_kv_values_over_the_text(A):
+    """ctx_v in the memory of ctx: values are placed after both products have read it."""
+    from harness import parity
+    for b, (k, v, kr, vr) in enumerate(_ctx_case(A, 256, [97, 33], 415, in_place=True)):
+        parity(k, kr, f"k {b}", quantum=kr)
+        parity(v, vr, f"v {b}", quantum=vr)
 
 
 @pytest.mark.parametrize("dim,heads,lat_h,lat_w", [(1024, 8, 26, 40), (256, 4, 7, 24)])

@@ -44,6 +44,7 @@ namespace {
 
 constexpr int BQ = 256;        // queries per work item
 constexpr int BKV = 64;        // keys per tile
+constexpr float kNoMax = -3.0e38f;   // a running max before any key: below every finite scaled score
 constexpr int NTHR = 512;      // threads per workgroup
 constexpr int LDS_AHEAD = 4;   // fragment reads in flight ahead of the MFMAs
 constexpr int NSLOT = 4;       // key and value tiles in LDS
@@ -234,7 +235,9 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int v = 0; v < 4; ++v) o[qb][db][v] = 0.f;
-  float m_run[2] = {-INFINITY, -INFINITY};   // running max (scaled, log2) of the lane's rows
+  // running max (scaled, log2) of the lane's rows; it starts finite, so that a piece
+  // whose scores all overflow to -inf weighs nothing in the merge (-inf - -inf is NaN)
+  float m_run[2] = {kNoMax, kNoMax};
   float l_run[2] = {0.f, 0.f};               // this lane's quarter of each running denominator
   f32x4 s[4][2];
   bf16x8 pf[2][2];
@@ -813,7 +816,7 @@ __global__ __launch_bounds__(64 * SM_WAVES, 1) void attn_small_kernel(const Attn
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int v = 0; v < 4; ++v) o[qb][db][v] = 0.f;
-  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
+  float m_run[2] = {kNoMax, kNoMax}, l_run[2] = {0.f, 0.f};
 
   for (int t = wave; t < S.n_tiles; t += SM_WAVES) {
     const int j0 = t * BKV;
@@ -901,7 +904,7 @@ __global__ __launch_bounds__(64 * SM_WAVES, 1) void attn_small_kernel(const Attn
   }
 
   // merge: o = sum_w 2^(m_w - M) o_w / sum_w 2^(m_w - M) l_w (a wave without
-  // tiles holds m = -inf and adds nothing)
+  // tiles adds nothing)
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {
     const float l_tot = rows4_sum(l_run[qb]);

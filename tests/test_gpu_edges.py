@@ -133,6 +133,25 @@ def test_attn_few_keys(A, hd, q_lens, caches):
         off += n
 
 
+@pytest.mark.parametrize("hd,q_len,cache", [(64, 40, 448), (128, 40, 448), (64, 700, 3840), (128, 700, 3840)])
+def test_attn_piece_of_overflowed_scores(A, hd, q_len, cache):
+    """Scores of every key past the first tile overflow to -inf: the waves (40
+    queries) and the pieces of a split (700) that hold no other keys weigh nothing."""
+    from harness import parity
+    from test_gpu_parity import _attn, _attn_case
+    sh = BlockShape(dim=4 * hd, n_heads=4, head_dim=hd, ffn_dim=512, frames=1, lat_h=4, lat_w=8)
+    pc, dims, batch, _, o, qs, ks, vs = _attn_case(A, sh, [q_len], [cache], 425)
+    q, k = np.abs(qs[0]) + 0.5, ks[0].copy()
+    q = host_f32(dev_bf16(q))
+    k[64:] = -np.float32(2.0 ** 127)
+    pc.fill_stream(0, k, vs[0])
+    pc.upload()
+    _attn(A, dims, batch, dev_bf16(q.reshape(q_len, -1)), pc.kv(A), o)
+    _sync()
+    ref = O.attention(q, k, vs[0]).reshape(q_len, -1)
+    parity(host_f32(o), ref, f"hd {hd} q {q_len}", quantum=ref)
+
+
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("ctx", [1, 37, 200])
 def test_block_few_text_keys(A, hd, ctx):

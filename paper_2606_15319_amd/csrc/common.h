@@ -131,6 +131,10 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
       reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const char*)p))));
 }
 
+// An attention's running maximum before any key: below every finite scaled score
+// (fp32 scores times log2(e) / sqrt(d) stay above -6.2e37 at d = 64).
+constexpr float kNoMax = -3.0e38f;
+
 __device__ __forceinline__ float gelu_tanh(float y) {
   // 0.5 y (1 + tanh z) = y * sigmoid(2 z) = y / (1 + 2^(-2 z log2(e))),
   // z = sqrt(2/pi) (y + 0.044715 y^3): one exp2 and one reciprocal; for large

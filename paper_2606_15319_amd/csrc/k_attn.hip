@@ -44,7 +44,6 @@ namespace {
 
 constexpr int BQ = 256;        // queries per work item
 constexpr int BKV = 64;        // keys per tile
-constexpr float kNoMax = -3.0e38f;   // a running max before any key: below every finite scaled score
 constexpr int NTHR = 512;      // threads per workgroup
 constexpr int LDS_AHEAD = 4;   // fragment reads in flight ahead of the MFMAs
 constexpr int NSLOT = 4;       // key and value tiles in LDS

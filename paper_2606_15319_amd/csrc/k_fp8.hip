@@ -348,7 +348,9 @@ __global__ __launch_bounds__(F8_NTHR, 1) void attn_fp8_kernel(const AttnArgs a) 
   for (int db = 0; db < 4; ++db)
 #pragma unroll
     for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
-  float m_run = -INFINITY;
+  // it starts finite, so that tiles before the first finite score (all overflowed to
+  // -inf) weigh nothing: -inf - -inf would be NaN
+  float m_run = kNoMax;
   float l_run = 0.f;
 
   // MFMA phase of position t: S^T = K Q^T of position t (two 32-key blocks, two

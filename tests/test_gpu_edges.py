@@ -133,23 +133,35 @@ def test_attn_few_keys(A, hd, q_lens, caches):
         off += n
 
 
-@pytest.mark.parametrize("hd,q_len,cache", [(64, 40, 448), (128, 40, 448), (64, 700, 3840), (128, 700, 3840)])
-def test_attn_piece_of_overflowed_scores(A, hd, q_len, cache):
-    """Scores of every key past the first tile overflow to -inf: the waves (40
-    queries) and the pieces of a split (700) that hold no other keys weigh nothing."""
-    from harness import parity
+@pytest.mark.parametrize("hd,q_len,cache,quant,finite", [
+    (64, 40, 448, 0, slice(0, 64)), (128, 40, 448, 0, slice(0, 64)),        # one wave's tile
+    (64, 700, 3840, 0, slice(0, 64)), (128, 700, 3840, 0, slice(0, 64)),    # one piece's tile
+    (64, 40, 448, 0, slice(256, 320)), (128, 700, 3840, 0, slice(3900, 4000)),
+    (128, 40, 448, 1, slice(0, 64)), (128, 40, 448, 1, slice(64, None)),    # the first tile, or all others
+    (128, 300, 640, 1, slice(500, 600)),
+])
+def test_attn_overflowed_scores(A, hd, q_len, cache, quant, finite):
+    """Scores of every key outside `finite` overflow to -inf: the waves (40 queries),
+    the pieces of a split (700) and the tiles before the first finite score weigh nothing."""
+    from harness import fp8_parity, parity
+    from oracle import fp8_ref
     from test_gpu_parity import _attn, _attn_case
     sh = BlockShape(dim=4 * hd, n_heads=4, head_dim=hd, ffn_dim=512, frames=1, lat_h=4, lat_w=8)
-    pc, dims, batch, _, o, qs, ks, vs = _attn_case(A, sh, [q_len], [cache], 425)
-    q, k = np.abs(qs[0]) + 0.5, ks[0].copy()
-    q = host_f32(dev_bf16(q))
-    k[64:] = -np.float32(2.0 ** 127)
+    pc, dims, _, _, o, qs, ks, vs = _attn_case(A, sh, [q_len], [cache], 425)
+    q = host_f32(dev_bf16(np.abs(qs[0]) + 0.5))
+    k = np.full_like(ks[0], -np.float32(2.0 ** 127))
+    k[finite] = ks[0][finite]
     pc.fill_stream(0, k, vs[0])
     pc.upload()
-    _attn(A, dims, batch, dev_bf16(q.reshape(q_len, -1)), pc.kv(A), o)
+    _attn(A, dims, A.Batch([q_len], [cache], quant=[quant]), dev_bf16(q.reshape(q_len, -1)), pc.kv(A), o)
     _sync()
-    ref = O.attention(q, k, vs[0]).reshape(q_len, -1)
-    parity(host_f32(o), ref, f"hd {hd} q {q_len}", quantum=ref)
+    got = host_f32(o).reshape(q_len, 4, hd)
+    if quant:
+        ref, _, sigma = fp8_ref.fp8_attention(q, k, vs[0], sigma=True)
+        fp8_parity(got, ref, sigma, f"fp8 q {q_len}")
+    else:
+        ref = O.attention(q, k, vs[0])
+        parity(got, ref, f"hd {hd} q {q_len}", quantum=ref)
 
 
 @pytest.mark.parametrize("hd", [64, 128])

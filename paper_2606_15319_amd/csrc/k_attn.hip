@@ -280,7 +280,10 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
   const size_t hs = static_cast<size_t>(PAGED ? a.T : S.T) * HD;
   int lw0 = 0, lw = 0;
   if (LIST) lw = list_window(0);
-  int fr = -1, pw0 = 0, pw = 0;
+  const size_t page_bytes = 2 * hs * a.H;   // of keys, and of values
+  const char* k_head = reinterpret_cast<const char*>(a.k + h * hs);
+  const char* v_head = reinterpret_cast<const char*>(a.v + h * hs);
+  int fr = -2, pw0 = 0, pw = 0;   // (-2: no frame, nor the one before frame 0)
   const char *kp0 = nullptr, *kp1 = nullptr, *vp0 = nullptr, *vp1 = nullptr;
   if (PAGED) {
     // (a stream of up to 64 frames needs one window, which does not wait for the list)
@@ -321,12 +324,22 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
           pw = page_window(f);
           asm volatile("" : "+v"(pw));
         }
+        // One product a page, and over consecutive frames one page a frame: where a
+        // frame is a tile or two long this runs every tile, and with the eight 64-bit
+        // scalar products of both pages' keys and values 2500 queries over 14596 keys,
+        // 20 heads of 64, frames of 64, took 320 us for 311.
+        if (!LIST && f == fr + 1) {
+          kp0 = kp1 + 2 * hs;
+          vp0 = vp1 + 2 * a.T;
+        } else {
+          const size_t p0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(pw, f - pw0)) * page_bytes;
+          kp0 = k_head + p0;
+          vp0 = v_head + p0;
+        }
+        const size_t p1 = static_cast<uint32_t>(__builtin_amdgcn_readlane(pw, f + 1 - pw0)) * page_bytes;
+        kp1 = k_head + p1 - 2 * hs;
+        vp1 = v_head + p1 - 2 * a.T;
         fr = f;
-        const int p0 = __builtin_amdgcn_readlane(pw, f - pw0), p1 = __builtin_amdgcn_readlane(pw, f + 1 - pw0);
-        kp0 = reinterpret_cast<const char*>(a.k + (static_cast<size_t>(p0) * a.H + h) * hs);
-        kp1 = reinterpret_cast<const char*>(a.k + (static_cast<size_t>(p1) * a.H + h) * hs) - 2 * hs;
-        vp0 = reinterpret_cast<const char*>(a.v + (static_cast<size_t>(p0) * a.H + h) * hs);
-        vp1 = reinterpret_cast<const char*>(a.v + (static_cast<size_t>(p1) * a.H + h) * hs) - 2 * a.T;
       }
     }
   };

@@ -133,6 +133,30 @@ def test_attn_few_keys(A, hd, q_lens, caches):
         off += n
 
 
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("lat,frames", [
+    ((4, 8), 150),    # 32 keys a frame: a tile is two frames, the page window moves twice
+    ((7, 8), 150),    # 56: tiles straddle frames at every offset
+    ((8, 8), 150),    # 64: a frame a tile
+    ((12, 16), 30),   # 192: three tiles a frame, one page window
+])
+def test_attn_page_walk(A, hd, lat, frames):
+    """Ranges of a split schedule that start inside a stream and walk its (shuffled)
+    pages, tile by tile and page by page."""
+    from harness import parity
+    from test_gpu_parity import _attn, _attn_case
+    T = lat[0] * lat[1]
+    sh = BlockShape(dim=8 * hd, n_heads=8, head_dim=hd, ffn_dim=512, frames=1, lat_h=lat[0], lat_w=lat[1])
+    q_len = 1025 if frames < 100 else 300   # (over 256 workgroups of 32 queries, or over 64 tiles)
+    pc, dims, batch, q, o, qs, ks, vs = _attn_case(A, sh, [q_len], [T * frames], 423)
+    _attn(A, dims, batch, q, pc.kv(A), o)
+    _sync()
+    got = host_f32(o).reshape(q_len, 8, hd)
+    for h in (0, 3, 7):
+        ref = O.attention(qs[0][:, h:h + 1], ks[0][:, h:h + 1], vs[0][:, h:h + 1])
+        parity(got[:, h:h + 1], ref, f"T {T} head {h}", quantum=ref)
+
+
 @pytest.mark.parametrize("hd,q_len,cache,quant,finite", [
     (64, 40, 448, 0, slice(0, 64)), (128, 40, 448, 0, slice(0, 64)),        # one wave's tile
     (64, 700, 3840, 0, slice(0, 64)), (128, 700, 3840, 0, slice(0, 64)),    # one piece's tile

@@ -526,7 +526,7 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
     }
     __builtin_amdgcn_sched_group_barrier(0x008, 2 * LDS_AHEAD, 0);
     __builtin_amdgcn_s_setprio(0);
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (HD == 128) __builtin_amdgcn_sched_barrier(0);
   };
 
   // softmax of the scores of the current position into pf (ends: the position's
@@ -591,8 +591,11 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
         pf[qb][ps] = __builtin_bit_cast(bf16x8, u32x4{pw[0], pw[1], pw[2], pw[3]});
       }
     }
-    // the weights and sums are formed here, in this phase
-    asm volatile("" : "+v"(pf[0][0]), "+v"(pf[0][1]), "+v"(pf[1][0]), "+v"(pf[1][1]), "+v"(l_run[0]), "+v"(l_run[1]));
+    // The weights and sums are formed here, in this phase.  At d = 64 the MFMA phase
+    // is half as long and cannot hide the whole softmax of the other group: there the
+    // compiler may carry a part of it into the products that follow.
+    if constexpr (HD == 128)
+      asm volatile("" : "+v"(pf[0][0]), "+v"(pf[0][1]), "+v"(pf[1][0]), "+v"(pf[1][1]), "+v"(l_run[0]), "+v"(l_run[1]));
   };
   const std::true_type yes;
   const std::false_type no;

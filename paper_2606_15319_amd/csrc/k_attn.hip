@@ -371,104 +371,72 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
   // range's ends the last tile, when keys run out inside it, and text of odd
   // length go through registers, zeroed past the end.  (Lane indices are taken
   // anew there: shared with the main loop they would stay in registers across it.)
-  // A list's items have few tiles, so there the partial tile takes one trip to
-  // memory, from the bases at hand: 11 kept tiles 38.7 -> 36.7 us, 52 of 512 with the
-  // selection 139.5 -> 136.6.  Over all tiles the trips hide (2 us of an item's 340),
-  // and the same code there cost the main loop 1% (37440 keys of 20 heads 1498 ->
-  // 1526 us, the large block 5703 -> 5780: other registers).
+  // The partial tile comes in 16-byte pieces from the bases at hand, NI trips to
+  // memory for its keys and NI for its values.  Element by element, with the page
+  // looked up again, its values took eight times as many, which only a long item
+  // hides: on a split schedule, whose ranges are short, 480 queries over 5984 keys,
+  // 12 heads, took 47.0 us for 44.9, and five streams of 720 over up to 5760, 9
+  // heads, 147 for 132.  (With the two trips of d = 128 issued together the long
+  // items' loop is up to 1% slower: other registers.)
   auto fetch = [&](int u) __attribute__((always_inline)) {
     if (u > 0 && u <= n) {
-      const int t = id;   // pairs are fetched in order: the tile of the keys before
-      if (VEC && t < nfull) {
+      // pairs are fetched in order: the tile of the keys before, whose bases are
+      // still at hand (move_to(u) comes after)
+      if (VEC && id < nfull) {
         dma_values(u - 1);
       } else {
         int ln = threadIdx.x & 63;
         asm volatile("" : "+v"(ln));
         const int dim = 8 * wave + (ln >> 3), key = 8 * ((ln & 7) ^ swz<BKV * 2>(dim));
-        const int left = kv_len - t * BKV - key;
+        const int left = kv_len - id * BKV - key, o_ = off0 + key;
+        const bf16_t* vb = reinterpret_cast<const bf16_t*>(PAGED && o_ >= a.T ? vp1 : vp0) + o_ +
+                           static_cast<size_t>(dim) * vstride;
         bf16_t* dst = &sV[((u - 1) % NSLOT) * TILE + wave * 512 + ln * 8];
-        if constexpr (LIST) {
-          static_assert(VEC && PAGED, "lists are of paged tiles");
-          // t's bases are still at hand (move_to(u) comes after).  Pieces of 8 keys are
-          // 16-byte aligned, and one that holds a key lies whole in its page's row.
-          const int o_ = off0 + key;
-          const bf16_t* vb = reinterpret_cast<const bf16_t*>(o_ >= a.T ? vp1 : vp0) + o_ +
-                             static_cast<size_t>(dim) * vstride;
-          u32x4 x[NI];
-#pragma unroll
+        if constexpr (VEC) {
+          // pieces of 8 keys are 16-byte aligned, and one that holds a key lies whole in
+          // its row of the page (or of the text): rows are multiples of 8 keys long
+#pragma unroll 1
           for (int j = 0; j < NI; ++j) {
-            x[j] = u32x4{0u, 0u, 0u, 0u};
-            if (left > 0) x[j] = *reinterpret_cast<const u32x4*>(vb + static_cast<size_t>(64 * j) * vstride);
-          }
-#pragma unroll
-          for (int j = 0; j < NI; ++j) {
+            u32x4 x = {0u, 0u, 0u, 0u};
+            if (left > 0) x = *reinterpret_cast<const u32x4*>(vb + static_cast<size_t>(64 * j) * vstride);
 #pragma unroll
             for (int i = 0; i < 4; ++i)   // (past the end the page may hold anything)
-              x[j][i] = 2 * i + 1 < left ? x[j][i] : (2 * i < left ? x[j][i] & 0xffffu : 0u);
-            *reinterpret_cast<u32x4*>(dst + j * 4096) = x[j];
+              x[i] = 2 * i + 1 < left ? x[i] : (2 * i < left ? x[i] & 0xffffu : 0u);
+            *reinterpret_cast<u32x4*>(dst + j * 4096) = x;
           }
         } else {
-          const TileMap m = map_tile<HD, PAGED>(a, S, h, t * BKV);
-          const int o_ = m.off0 + key;
-          const bf16_t* vb = (o_ < m.T ? m.v0 + o_ : m.v1 + (o_ - m.T)) + static_cast<size_t>(dim) * vstride;
-          if constexpr (VEC) {
-#pragma unroll 1
-            for (int j = 0; j < NI; ++j)
-#pragma unroll 1
-              for (int e = 0; e < 8; ++e)
-                dst[j * 4096 + e] = e < left ? vb[static_cast<size_t>(64 * j) * vstride + e] : bf16_t(0);
-          } else {
-            // Every tile comes this way when a text's length is no multiple of 8: all
-            // its loads together (one after the other, a block step over 511 text
-            // tokens took 669 us for 637, five streams of which two are odd 428 for 407).
-            bf16_t x[NI][8];
+          // Every tile comes this way when a text's length is no multiple of 8: all
+          // its loads together (one after the other, a block step over 511 text
+          // tokens took 669 us for 637, five streams of which two are odd 428 for 407).
+          bf16_t x[NI][8];
 #pragma unroll
-            for (int j = 0; j < NI; ++j)
+          for (int j = 0; j < NI; ++j)
 #pragma unroll
-              for (int e = 0; e < 8; ++e)
-                x[j][e] = e < left ? vb[static_cast<size_t>(64 * j) * vstride + e] : bf16_t(0);
+            for (int e = 0; e < 8; ++e)
+              x[j][e] = e < left ? vb[static_cast<size_t>(64 * j) * vstride + e] : bf16_t(0);
 #pragma unroll
-            for (int j = 0; j < NI; ++j)
+          for (int j = 0; j < NI; ++j)
 #pragma unroll
-              for (int e = 0; e < 8; ++e) dst[j * 4096 + e] = x[j][e];
-          }
+            for (int e = 0; e < 8; ++e) dst[j * 4096 + e] = x[j][e];
         }
       }
     }
     if (u < n) {
       move_to(u);
-      const int t = id;
-      if (t < nfull) {
+      if (id < nfull) {
         dma_keys(u);
       } else {   // (a partial tile's values come with the next pair, through registers)
         int ln = threadIdx.x & 63;
         asm volatile("" : "+v"(ln));
-        if constexpr (LIST) {
-          u32x4 x[NI];
-#pragma unroll
-          for (int j = 0; j < NI; ++j) {
-            const int R = (wave * NI + j) * KROWS + ln / CPR;
-            const int key = kappa16(R >> 4, R & 15), o_ = off0 + key;
-            const bf16_t* b = reinterpret_cast<const bf16_t*>(o_ >= a.T ? kp1 : kp0) +
-                              static_cast<ptrdiff_t>(o_) * HD + 8 * ((ln % CPR) ^ swz<HD * 2>(R & 15));
-            x[j] = u32x4{0u, 0u, 0u, 0u};
-            if (t * BKV + key < kv_len) x[j] = *reinterpret_cast<const u32x4*>(b);
-          }
-#pragma unroll
-          for (int j = 0; j < NI; ++j)
-            *reinterpret_cast<u32x4*>(&sK[(u % NSLOT) * TILE + (wave * NI + j) * 512 + ln * 8]) = x[j];
-        } else {
-          const TileMap m = map_tile<HD, PAGED>(a, S, h, t * BKV);
 #pragma unroll 1
-          for (int j = 0; j < NI; ++j) {
-            const int R = (wave * NI + j) * KROWS + ln / CPR;
-            const int key = kappa16(R >> 4, R & 15), o_ = m.off0 + key;
-            const bf16_t* b = (o_ < m.T ? m.k0 + static_cast<size_t>(o_) * HD : m.k1 + static_cast<size_t>(o_ - m.T) * HD) +
-                              8 * ((ln % CPR) ^ swz<HD * 2>(R & 15));
-            u32x4 x = {0u, 0u, 0u, 0u};
-            if (t * BKV + key < kv_len) x = *reinterpret_cast<const u32x4*>(b);
-            *reinterpret_cast<u32x4*>(&sK[(u % NSLOT) * TILE + (wave * NI + j) * 512 + ln * 8]) = x;
-          }
+        for (int j = 0; j < NI; ++j) {
+          const int R = (wave * NI + j) * KROWS + ln / CPR;
+          const int key = kappa16(R >> 4, R & 15), o_ = off0 + key;
+          const bf16_t* b = reinterpret_cast<const bf16_t*>(PAGED && o_ >= a.T ? kp1 : kp0) +
+                            static_cast<ptrdiff_t>(o_) * HD + 8 * ((ln % CPR) ^ swz<HD * 2>(R & 15));
+          u32x4 x = {0u, 0u, 0u, 0u};
+          if (id * BKV + key < kv_len) x = *reinterpret_cast<const u32x4*>(b);
+          *reinterpret_cast<u32x4*>(&sK[(u % NSLOT) * TILE + (wave * NI + j) * 512 + ln * 8]) = x;
         }
       }
     }

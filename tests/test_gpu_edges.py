@@ -118,6 +118,7 @@ def test_block_small_products(A, dim, heads, lat_h, lat_w):
     (128, [64], [4096]),                # 65 tiles, 4 items: a split of 32 workgroups
     (64, [2048, 8], [0, 1920]),         # 260 workgroups: one workgroup per item
     (64, [700], [3840]),                # 71 tiles on 12 items: a split schedule below 256 workgroups
+    (128, [203], [4192]),               # the same at d = 128, 43 keys in the last tile
 ])
 def test_attn_few_keys(A, hd, q_lens, caches):
     from harness import parity

@@ -772,7 +772,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const AttnArgs a) {
 // pieces, about 5 us for the eight waves' tiles at d = 128).
 constexpr int SM_BQ = 32;      // queries per workgroup
 constexpr int SM_WAVES = 8;
-constexpr int SM_TILES = 64;   // most key tiles of a stream
+// most key tiles of a stream (plan_attention)
+constexpr int small_tiles(int head_dim) { return head_dim == 128 ? 31 : 47; }
 
 template <int HD, bool PAGED, bool VEC>
 __global__ __launch_bounds__(64 * SM_WAVES, 1) void attn_small_kernel(const AttnArgs a) {
@@ -1176,10 +1177,16 @@ void plan_attention(AttnArgs& a, int head_dim, float* split_ws) {
   a.part_o = nullptr;
   a.part_ml = nullptr;
   // Few queries over few keys: 32-query workgroups while they fit one round of
-  // the CUs and the longest stream has at most 64 tiles, eight per wave.  At 240
-  // workgroups (40 heads, 192 queries) 9 tiles take 16.5 us for 22.4 and 24 take
-  // 31 for 48; at 180 (12 heads, 480 queries) 60 tiles 54 for 109.  Past one
-  // round it loses: 480 workgroups 52 us for 36 (60 tiles), 576: 84 for 49 (24).
+  // the CUs and the longest stream has so few tiles that a wave's share of them
+  // takes no longer than the split schedule below, whose pieces have eight tiles
+  // each and a merge behind them: up to 31 tiles at d = 128, 47 at d = 64.  us here
+  // and split, d = 128: 192 queries, 12 heads, 16 tiles 21.4 / 24.4, 28 32.1 / 33.8,
+  // 32 36.4 / 26.7, 64 66.2 / 30.8; 40 heads, 28 33.5 / 36.3, 32 37.2 / 29.1, 64
+  // 66.6 / 44.3; 1024, 8 heads, 28 32.9 / 39.9, 32 36.9 / 33.2, 64 66.3 / 35.6.  d =
+  // 64: 192, 20 heads, 40 22.9 / 28.1, 48 26.3 / 23.7, 64 33.3 / 26.4.  With items
+  // that neither splits: 240 workgroups (40 heads, 192 queries) 9 tiles 16.5 for
+  // 22.4.  Past one round it loses: 480 workgroups 52 us for 36 (60 tiles), 576: 84
+  // for 49 (24).
   {
     int64_t wgs = 0;
     int most = 0;
@@ -1187,7 +1194,7 @@ void plan_attention(AttnArgs& a, int head_dim, float* split_ws) {
       wgs += static_cast<int64_t>((tmp[i].q_len + SM_BQ - 1) / SM_BQ) * a.H;
       most = tmp[i].n_tiles > most ? tmp[i].n_tiles : most;
     }
-    if (items > 0 && wgs <= kAttnSplitBlocks && most <= SM_TILES) {
+    if (items > 0 && wgs <= kAttnSplitBlocks && most <= small_tiles(head_dim)) {
       a.small = 1;
       a.total_items = static_cast<int32_t>(wgs);
       a.per_xcd = (a.total_items + kNumXcd - 1) / kNumXcd;

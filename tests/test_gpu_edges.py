@@ -109,13 +109,17 @@ def test_block_small_products(A, dim, heads, lat_h, lat_w):
     parity(host_f32(run.out), ref["out"], f"block {dim}")
 
 
-# 32-query workgroups with the keys split between waves: up to 256 workgroups
-# and 64 key tiles; past either the items run whole or on a split schedule.
+# 32-query workgroups with the keys split between waves: up to 256 workgroups and
+# 31 key tiles (d = 64: 47); past either the items run whole or on a split schedule.
 @pytest.mark.parametrize("hd,q_lens,caches", [
     (64, [1, 33], [0, 512]),            # one query, one key; 9 tiles: a wave takes two
     (128, [31, 64, 5], [448, 64, 0]),   # 8 tiles and a ragged end, lengths off every multiple
-    (128, [64], [4032]),                # 64 tiles: the longest taken
-    (128, [64], [4096]),                # 65 tiles, 4 items: a split of 32 workgroups
+    (128, [64], [4032]),                # 64 tiles, 4 items: a split of 32 workgroups
+    (128, [64], [4096]),                # 65 tiles, the same
+    (128, [64, 40], [1920, 96]),        # 31 tiles: the longest taken
+    (128, [64, 40], [1984, 96]),        # 32 tiles: a split
+    (64, [33], [2944]),                 # 47 tiles: the longest taken
+    (64, [33], [3008]),                 # 48 tiles: a split
     (64, [2048, 8], [0, 1920]),         # 260 workgroups: one workgroup per item
     (64, [700], [3840]),                # 71 tiles on 12 items: a split schedule below 256 workgroups
     (128, [203], [4192]),               # the same at d = 128, 43 keys in the last tile

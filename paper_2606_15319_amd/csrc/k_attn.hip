@@ -367,12 +367,21 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
     for (int j = 0; j < NI; ++j)
       lds_dma16(v_prev + static_cast<size_t>(j) * 128 * vstride, dst + 8192u * j);
   };
+  // Base (text: p) that offset o_ of the current tile counts from, taken anew from
+  // the page window; `over` bytes are one page's offsets.  (With kp0 .. vp1 used here
+  // too, the d = 64 loop kept them in vector registers, 148 for 128 a lane: below.)
+  auto tile_base = [&](const char* p, const char* head, int o_, size_t over) __attribute__((always_inline)) {
+    if constexpr (!PAGED) return p;
+    const size_t p0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(pw, fr - pw0)) * page_bytes;
+    const size_t p1 = static_cast<uint32_t>(__builtin_amdgcn_readlane(pw, fr + 1 - pw0)) * page_bytes;
+    return head + (o_ >= a.T ? p1 - over : p0);
+  };
   // Pair u: the keys of position u and the values of position u - 1.  At the
   // range's ends the last tile, when keys run out inside it, and text of odd
   // length go through registers, zeroed past the end.  (Lane indices are taken
   // anew there: shared with the main loop they would stay in registers across it.)
-  // The partial tile comes in 16-byte pieces from the bases at hand, NI trips to
-  // memory for its keys and NI for its values.  Element by element, with the page
+  // The partial tile comes in 16-byte pieces, NI trips to memory for its keys and
+  // NI for its values.  Element by element, with the page
   // looked up again, its values took eight times as many, which only a long item
   // hides: on a split schedule, whose ranges are short, 480 queries over 5984 keys,
   // 12 heads, took 47.0 us for 44.9, and five streams of 720 over up to 5760, 9
@@ -380,8 +389,8 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
   // items' loop is up to 1% slower: other registers.)
   auto fetch = [&](int u) __attribute__((always_inline)) {
     if (u > 0 && u <= n) {
-      // pairs are fetched in order: the tile of the keys before, whose bases are
-      // still at hand (move_to(u) comes after)
+      // pairs are fetched in order: id, off0 and fr are those of the keys before
+      // (move_to(u) comes after)
       if (VEC && id < nfull) {
         dma_values(u - 1);
       } else {
@@ -389,7 +398,7 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
         asm volatile("" : "+v"(ln));
         const int dim = 8 * wave + (ln >> 3), key = 8 * ((ln & 7) ^ swz<BKV * 2>(dim));
         const int left = kv_len - id * BKV - key, o_ = off0 + key;
-        const bf16_t* vb = reinterpret_cast<const bf16_t*>(PAGED && o_ >= a.T ? vp1 : vp0) + o_ +
+        const bf16_t* vb = reinterpret_cast<const bf16_t*>(tile_base(vp0, v_head, o_, 2 * a.T)) + o_ +
                            static_cast<size_t>(dim) * vstride;
         bf16_t* dst = &sV[((u - 1) % NSLOT) * TILE + wave * 512 + ln * 8];
         if constexpr (VEC) {
@@ -432,7 +441,7 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
         for (int j = 0; j < NI; ++j) {
           const int R = (wave * NI + j) * KROWS + ln / CPR;
           const int key = kappa16(R >> 4, R & 15), o_ = off0 + key;
-          const bf16_t* b = reinterpret_cast<const bf16_t*>(PAGED && o_ >= a.T ? kp1 : kp0) +
+          const bf16_t* b = reinterpret_cast<const bf16_t*>(tile_base(kp0, k_head, o_, 2 * hs)) +
                             static_cast<ptrdiff_t>(o_) * HD + 8 * ((ln % CPR) ^ swz<HD * 2>(R & 15));
           u32x4 x = {0u, 0u, 0u, 0u};
           if (id * BKV + key < kv_len) x = *reinterpret_cast<const u32x4*>(b);
@@ -632,9 +641,11 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
   if (slot >= 0) __syncthreads();   // a following range reuses the tiles
 }
 
-// One workgroup per item.
+// One workgroup per item.  At d = 64 past one round two workgroups share a CU (64 KB
+// of LDS each), if a lane takes at most 128 registers: five streams of 3328 queries
+// over 17728 keys, 20 heads, 2190 us with 148, 1760 so.
 template <int HD, bool PAGED, bool VEC>
-__global__ __launch_bounds__(NTHR, 1) void attn_kernel(const AttnArgs a) {
+__global__ __launch_bounds__(NTHR, HD == 64 ? 4 : 1) void attn_kernel(const AttnArgs a) {
   __shared__ __attribute__((aligned(16))) bf16_t sK[NSLOT * BKV * HD];
   __shared__ __attribute__((aligned(16))) bf16_t sV[NSLOT * HD * BKV];
 

@@ -206,14 +206,8 @@ __global__ __launch_bounds__(256) void fp8_kv_prep_kernel(const AttnArgs a, int 
 }
 
 // ------------------------------------------------------------ attention
-// LDS row of physical key p of a tile: key block b = p / 32 holds in MFMA row
+// Key of LDS row R of a tile: key block b = R / 32 holds in MFMA row
 // r = 8 (i / 4) + 4 h + i % 4 the key 32 b + 16 h + i.
-__device__ __forceinline__ int f8_lds_row(int p) {
-  const int b = p >> 5, h = (p >> 4) & 1, i = p & 15;
-  return 32 * b + 8 * (i >> 2) + 4 * h + (i & 3);
-}
-
-// Key of LDS row R of a tile: the inverse of the order above.
 __device__ __forceinline__ int f8_row_key(int R) {
   const int r = R & 31;
   return 32 * (R >> 5) + 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3);

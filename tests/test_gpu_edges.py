@@ -256,15 +256,61 @@ def test_attn_sparse_few_tiles(A, quant, keys):
         parity(got, ref, f"keys {keys}", quantum=ref)
 
 
-@pytest.mark.parametrize("q_lens", [[3328, 3328], [2500, 4096], [3072, 3500]])
-def test_attn_full_rounds_and_split_rest(A, q_lens):
-    """260 to 280 items of 10 heads.  Two streams of 52 tiles fill one round whole
-    and split its last four items, which lie in the second stream; streams of
-    different length (40 and 64 tiles, 48 and 55) run one workgroup per item."""
+@pytest.mark.parametrize("tiles", [256, 257, 512, 513, 1024, 1025])
+def test_sparse_select_key_registers(A, tiles):
+    """The selection holds a stream's scores in 4, 8 or 16 registers a lane, or in LDS,
+    by the longest stream: both sides of each line, beside a short stream."""
+    from test_gpu_parity import _attn_case, _check_selection, _sparse_rows
+    import oracle.sparse_ref as SR
+    sh = BlockShape(dim=128, n_heads=2, head_dim=64, ffn_dim=128, frames=1, lat_h=8, lat_w=8)
+    q_lens, caches, rho = [40, 70], [64 * (tiles - 1), 640], [0.9, 0.6]
+    pc, dims, _, q, o, qs, ks, vs = _attn_case(A, sh, q_lens, caches, 431)
+    batch = A.Batch(q_lens, caches, sparsity=rho)
+    rows = _sparse_rows(A, dims, batch, q, pc.kv(A), row_stride=SR.keep_count(tiles, rho[0]))
+    _sync()
+    for b in range(2):
+        _check_selection(rows[2 * b:2 * b + 2], qs[b], ks[b], rho[b], 2, f"{tiles} tiles stream {b}")
+
+
+@pytest.mark.parametrize("hd,quant", [(64, 0), (128, 0), (128, 1)])
+def test_attn_sparse_long_lists(A, hd, quant):
+    """Lists of 155 tiles: the kernels hold 64 entries at a time and refill twice."""
+    import oracle.sparse_ref as SR
+    from harness import fp8_parity, parity
+    from oracle import fp8_ref
+    from test_gpu_parity import _attn, _attn_case
+    sh = BlockShape(dim=2 * hd, n_heads=2, head_dim=hd, ffn_dim=256, frames=1, lat_h=8, lat_w=12)
+    q_len, cache, rho = 41, 16416, 0.4
+    n, keys = 258, q_len + cache
+    pc, dims, _, q, o, qs, ks, vs = _attn_case(A, sh, [q_len], [cache], 432)
+    _attn(A, dims, A.Batch([q_len], [cache], sparsity=[rho], quant=[quant]), q, pc.kv(A), o)
+    _sync()
+    keep = SR.keep_count(n, rho)
+    assert -(-keys // 64) == n and keep == 155
+    lists = SR.select_blocks(SR.block_scores(qs[0], ks[0]), keep)
+    got = host_f32(o).reshape(q_len, 2, hd)
+    if quant:
+        mask = np.stack([SR.block_mask(lists[h], q_len, keys) for h in range(2)])
+        ref, _, sigma = fp8_ref.fp8_attention(qs[0], ks[0], vs[0], mask=mask, sigma=True)
+        fp8_parity(got, ref, sigma, "fp8")
+    else:
+        ref = SR.sparse_attention(qs[0], ks[0], vs[0], lists)
+        parity(got, ref, f"hd {hd}", quantum=ref)
+
+
+@pytest.mark.parametrize("q_lens,caches", [
+    ([3328, 3328], [0, 0]),     # 52 tiles each: the last four of 260 items, in the second stream
+    ([2300, 2304, 2290, 2304], [384] * 4),   # 42 tiles: the last 104 of 360, from the middle of one stream on
+    ([2500, 4096], [0, 0]),     # 40 and 64 tiles: no split
+    ([3072, 3500], [0, 0]),     # 48 and 55
+])
+def test_attn_full_rounds_and_split_rest(A, q_lens, caches):
+    """More items (of 10 heads) than a round holds: with equal tiles the full rounds run
+    whole and the rest is split; streams of different length run one workgroup per item."""
     from harness import parity
     from test_gpu_parity import _attn, _attn_case
     sh = BlockShape(dim=640, n_heads=10, head_dim=64, ffn_dim=512, frames=1, lat_h=8, lat_w=8)
-    pc, dims, batch, q, o, qs, ks, vs = _attn_case(A, sh, q_lens, [0, 0], 440)
+    pc, dims, batch, q, o, qs, ks, vs = _attn_case(A, sh, q_lens, caches, 440)
     _attn(A, dims, batch, q, pc.kv(A), o)
     _sync()
     og, off = host_f32(o), 0

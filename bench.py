@@ -272,8 +272,6 @@ def sp2_main(args):
         "probe": "one GPU's share of Ulysses SP2",
         "workload": f"{wl.name}: {H} of {wl.shape.n_heads} heads of {d}, {L} queries over {L_k} "
                     f"keys through the stream's pages", "items": items,
-        # (items of equal cost: one round of 256, or the last of up to four, partly idle)
-        "split_schedule": items <= 4 * 256 and 0 < items % 256 < 3 * 256 // 4,
         "ms_per_launch": round(avg, 4), "launches": n, "gflop": round(flops / 1e9, 1),
         "tflops": round(tf, 1), "frac": round(tf / PEAK_BF16_TFLOPS, 4),
         "frac_of_measured": round(tf / meas["mfma_bf16_tflops"], 4)}), flush=True)

@@ -160,7 +160,8 @@ __device__ __forceinline__ void store_partial(const AttnArgs& a, size_t slot,
 //
 // What bounds it: the matrix pipe (64 MFMAs of 16 clocks a wave and tile), the
 // issue port that MFMAs (8 clocks each) and vector instructions (4; exponentials
-// 8) share, and, on long calls, the card's power.  Two waves share a SIMD, w and
+// 8) share, at a clock that the card lowers under the load (2.17 GHz of 2.4 over
+// 32760 keys of 12 heads, 1.95 over 37440 of 40).  Two waves share a SIMD, w and
 // w + 4.  When all eight met at a barrier every tile they ran in step: both in
 // the products, then both in the softmax, about 4000 clocks a tile where the
 // products take 2048.  So the two halves of the workgroup are a half tile
@@ -299,8 +300,8 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
   const char* v_prev = nullptr;   // this lane's value address of the position moved to last
   int off0 = 0;
   // tile of the position moved to last: a list's entry read again for the values of the
-  // first and last pairs was a trip to memory each (14040 keys of 12 heads 347 -> 344 us,
-  // 52 kept tiles of an item 137.0 -> 136.0)
+  // first and last pairs was a trip to memory each (14040 keys of 12 heads 347.5 ->
+  // 344.5 us, 52 kept tiles of 512 with their selection 138.7 -> 137.5)
   int id = tb;
   // moves to position u < n: tile, page bases, off0
   auto move_to = [&](int u) __attribute__((always_inline)) {
@@ -777,10 +778,11 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const AttnArgs a) {
 // wave reads its K and V fragments straight from memory (the tiles are not
 // shared between waves, so LDS would add a trip and two barriers), in the
 // layouts attn_kernel reads from LDS; the waves' partial results meet in LDS at
-// the end.  192 queries over 576 keys, 4 heads of 64 (the tiny block): 15.9 us
-// on one workgroup per item, 9.5 here; 480 over 1440, 12 heads of 128: 47.8, 25.7.
-// What bounds it is the fragment loads (32 KB a wave and tile in 64-byte
-// pieces, about 5 us for the eight waves' tiles at d = 128).
+// the end.  192 queries over 576 keys, 4 heads of 64 (the tiny block): 15.7 us
+// on one workgroup per item, 8.6 here; 480 over 1440, 12 heads of 128: 46.8, 28.1.
+// What bounds it is the chain of a wave's tiles: the fragment loads of one (32 KB in
+// 64-byte pieces at d = 128) are issued together, but with K, V, O and Q in 256
+// registers there is no room to ask for the next tile's.
 constexpr int SM_BQ = 32;      // queries per workgroup
 constexpr int SM_WAVES = 8;
 // most key tiles of a stream (plan_attention)
@@ -1223,12 +1225,16 @@ void plan_attention(AttnArgs& a, int head_dim, float* split_ws) {
   // quarter of them idle: every item keeps its first W tiles (W = the even
   // share of all tiles per workgroup) and the idle workgroups take equal ranges
   // of the remaining tails.  Items of one head still run their main parts in
-  // step, sharing key tiles through L2.  The tail ranges cost more per tile
-  // (short segments, partial writes, the merge), which outweighs the gain when
-  // few workgroups are idle (228 items of 220 tiles, 28 workgroups idle: 426 us split,
-  // 352 whole).  The round is cut to as many workgroups as have
-  // eight tiles each (a multiple of the XCDs; 1440 queries over 4320 keys, 4 heads
-  // of 64, 1632 tiles on 24 items: 92 us unsplit, 34 on 200 workgroups).
+  // step, sharing key tiles through L2.  The tail ranges cost more per tile (short
+  // segments, partial writes, the merge) and end last, which outweighs the gain
+  // while few workgroups are idle.  Whole and split, us at d = 128: 28 idle (228
+  // items) 78 tiles 125 / 191, 220 330 / 396, 512 765 / 817; 56 idle 78 120 / 151,
+  // 220 320 / 332, 313 455 / 450, 512 739 / 709; 64 idle 78 120 / 129, 128 188 /
+  // 191, 220 316 / 304, 512 732 / 668.  (So from about a quarter idle on it depends
+  // on the tiles too, which the rule does not weigh.)  The round is cut to as many
+  // workgroups as have eight tiles each (a multiple of the XCDs; 1440 queries over
+  // 4320 keys, 4 heads of 64, 1632 tiles on 24 items: 92 us unsplit, 34 on 200
+  // workgroups).
   //
   // Items of equal cost that fill one to three rounds and leave more than a
   // quarter of the last one idle run their full rounds whole and split the rest

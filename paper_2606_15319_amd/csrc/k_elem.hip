@@ -800,7 +800,7 @@ __device__ __forceinline__ float silu(float v) { return v / (1.0f + expf(-v)); }
 // rows share one fp32 read of x from the caches and 2 R loads are in flight.
 // A load's eight products are summed by themselves before they join the lane's
 // sum: chains of 8 and K / 512 terms in place of one of K / 64 (error against
-// 64 bits at K = 5120: 1.8e-7, one chain 2.7e-7).
+// 64 bits at K = 5120: 1.8e-7, one chain 2.6e-7).
 // The activation sits at the output: as an input activation every row
 // evaluated it again over all of x (the 30720 x 5120 product of one stream
 // took 284 us that way, 1.1 TB/s, with 2-byte loads; all four kernels of that

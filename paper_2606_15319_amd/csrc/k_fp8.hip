@@ -213,7 +213,7 @@ __device__ __forceinline__ int f8_row_key(int R) {
   return 32 * (R >> 5) + 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3);
 }
 
-// What bounds it: vector issue (about 190 instructions a wave and tile beside 8
+// What bounds it: vector issue (about 200 instructions a wave and tile beside 8
 // MFMAs; exponentials and E4M3 conversions take 8 clocks of the port, most others
 // 4) and how few of them one wave alone can issue.  As in the bf16 kernel the two
 // waves of a SIMD run half a tile apart, one barrier a position, group 0 before

@@ -360,7 +360,8 @@ __global__ __launch_bounds__(NT, 1) void gemm_kernel(const bf16_t* __restrict__ 
 // Products of a few hundred rows leave most CUs without a 128 x 256 tile and
 // run at the latency of one tile's K loop, about 0.9 us a step with two steps
 // in flight (text keys and values of 589 tokens, 1536 wide: 50 us in four
-// launches, now 18 us in two; the tiny block, 192 rows of 256: 101 -> 64 us).  Here tiles are small (64 x 128 on eight waves, or 32 x 64 on
+// launches, now 17 us in two; the tiny block's step, 192 rows of 256: 101 -> 65
+// us).  Here tiles are small (64 x 128 on eight waves, or 32 x 64 on
 // four, so more CUs take part) and S - 1 steps are in flight through a ring of
 // S LDS stages: at K = 256 a tile's whole operands are requested at once.  One
 // barrier per step: it publishes stage kt and closes the reads of stage kt-1,

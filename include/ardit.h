@@ -208,11 +208,11 @@ int ardit_kv_append(hipStream_t stream, const ardit_dims* dims, const ardit_batc
  * equal length and leave the last of a few rounds of it partly idle, key ranges
  * are split between workgroups and the partial results combined through the
  * workspace.  The schedule depends on the whole batch, and a split sums in another
- * order, so a stream's rows may differ in rounding alone and in a batch.
- * When batch->sparsity gives some stream rho > 0 the
- * attention is block-sparse: each query tile attends only to the keys of the
- * tiles ardit_sparse_select would list for it (selection and attention both
- * run in this call, the lists live in the workspace). */
+ * order, so a stream's rows may differ in rounding alone and in a batch.  When
+ * batch->sparsity gives some stream rho > 0 the attention is block-sparse: each
+ * query tile attends only to the keys of the tiles ardit_sparse_select would list
+ * for it (selection and attention both run in this call, the lists live in the
+ * workspace). */
 int ardit_attn_fwd(hipStream_t stream, const ardit_dims* dims, const ardit_batch* batch,
                    const void* q, const ardit_kv_paged* kv, void* o, void* ws, size_t ws_bytes);
 
@@ -232,10 +232,10 @@ int ardit_attn_fwd(hipStream_t stream, const ardit_dims* dims, const ardit_batch
  * is loaded and kept until the process ends, and every call on that GPU
  * shares it: calls that overlap on one GPU (two streams, two threads) race on
  * it and must be ordered by the caller (whether a dense call splits, and so uses
- * it, depends on the whole batch; take it that every call does).  Nothing needs clearing between calls
- * (every scratch entry is written before it is read).  The call makes no
- * device or host allocation, no memset and no copy; it records no timing
- * events and skips ardit_debug_checks. */
+ * it, depends on the whole batch; take it that every call does).  Nothing needs
+ * clearing between calls (every scratch entry is written before it is read).  The
+ * call makes no device or host allocation, no memset and no copy; it records no
+ * timing events and skips ardit_debug_checks. */
 int ardit_attn_fwd_noalloc(hipStream_t stream, const ardit_dims* dims, const ardit_batch* batch,
                            const void* q, const ardit_kv_paged* kv, void* o);
 

@@ -1154,6 +1154,46 @@ size_t attention_split_bytes(int head_dim) {
   return static_cast<size_t>(2) * kAttnSplitBlocks * BQ * (head_dim + 2) * sizeof(float);
 }
 
+namespace {
+
+// When a split schedule ends, in 64ths of a tile after the time of a whole item
+// without its tiles.  A range's pieces after the first cost a start and a partial
+// store each (7.9 us at d = 128, 2.6 at d = 64), every schedule the merge's launch,
+// and every partial tile its trip to memory and back.  Fitted to 222 calls of one
+// round or less (8 to 200 items of 11 to 120 tiles), each timed whole and split;
+// the rule takes the slower side by at most 5% in any of them.  Before it every
+// round cut below 256 workgroups was split, and the short tails of items of 11 to 15
+// tiles put two and three pieces into a range: us whole and split, d = 128: 36 items
+// of 14 tiles 28.8 / 43.6, 176 of 11 27.9 / 49.5, streams of 4 to 31 tiles, 100
+// items, 53.0 / 85.0; 36 items of 16, one piece a range, 31.5 / 29.1; of 18, two, 34.1 /
+// 36.9; of 24, two, 42.4 / 37.9.
+int64_t split_end(const AttnStream* s, int n, int split_tiles, int64_t tails, int head_dim) {
+  const int64_t S = split_tiles;
+  int32_t pieces[kAttnSplitBlocks] = {};   // of each tail range
+  int64_t parts = 0;
+  int longest = 0;
+  for (int i = 0; i < n; ++i) {
+    longest = max(longest, s[i].main_tiles);
+    const int tl = s[i].n_tiles - s[i].main_tiles;
+    const int64_t t0 = s[i].tail_begin, t1 = i + 1 < n ? s[i + 1].tail_begin : tails;
+    if (t0 == t1) continue;
+    parts += (t1 - t0) / tl;   // main parts
+    for (int64_t r = t0 / S; r * S < t1; ++r) {
+      const int64_t lo = max(r * S, t0) - t0, hi = min((r + 1) * S, t1) - t0;
+      const int c = static_cast<int>((hi - 1) / tl - lo / tl + 1);
+      pieces[r] += c;
+      parts += c;
+    }
+  }
+  int most = 0;
+  for (int r = 0; r < kAttnSplitBlocks; ++r) most = max(most, pieces[r]);
+  const bool wide = head_dim == 128;
+  const int64_t last = S + (wide ? 5 : 2) * (most - 1);
+  return 64 * max(static_cast<int64_t>(longest), last) + (wide ? 320 + parts : 128 + 2 * parts);
+}
+
+}  // namespace
+
 void plan_attention(AttnArgs& a, int head_dim, float* split_ws) {
   // order streams by decreasing key count so the longest items start first
   AttnStream tmp[kMaxStreams];
@@ -1234,7 +1274,7 @@ void plan_attention(AttnArgs& a, int head_dim, float* split_ws) {
   // on the tiles too, which the rule does not weigh.)  The round is cut to as many
   // workgroups as have eight tiles each (a multiple of the XCDs; 1440 queries over
   // 4320 keys, 4 heads of 64, 1632 tiles on 24 items: 92 us unsplit, 34 on 200
-  // workgroups).
+  // workgroups), and split only where that ends sooner (split_end).
   //
   // Items of equal cost that fill one to three rounds and leave more than a
   // quarter of the last one idle run their full rounds whole and split the rest
@@ -1267,11 +1307,13 @@ void plan_attention(AttnArgs& a, int head_dim, float* split_ws) {
       const int here = tmp[i].n_qtiles * a.H - min(tmp[i].n_qtiles * a.H, max(0, item0 - tmp[i].item_begin));
       tails += static_cast<int64_t>(here) * (tmp[i].n_tiles - tmp[i].main_tiles);
     }
-    if (tails > 0) {
+    const int split_tiles = static_cast<int>((tails + spare - 1) / spare);
+    if (tails > 0 &&
+        split_end(tmp, n, split_tiles, tails, head_dim) < 64 * static_cast<int64_t>(tmp[0].n_tiles)) {
       a.item0 = item0;
       a.split_blocks = blocks;
       a.total_tiles = static_cast<int32_t>(tails);
-      a.split_tiles = static_cast<int32_t>((tails + spare - 1) / spare);
+      a.split_tiles = split_tiles;
       a.part_o = split_ws;
       a.part_ml = split_ws + static_cast<size_t>(2) * kAttnSplitBlocks * BQ * head_dim;
       a.per_xcd = blocks / kNumXcd;

@@ -138,6 +138,35 @@ def test_attn_few_keys(A, hd, q_lens, caches):
         off += n
 
 
+@pytest.mark.parametrize("hd,heads,q_lens,caches,split", [
+    (128, 12, [768], [64], False), (128, 12, [768], [128], False),   # 36 items of 13 and 14 tiles
+    (128, 12, [768], [256], True),                      # of 16: one piece of 8 tiles a range
+    (64, 16, [256] * 4, [448] * 4, False),              # 64 items of 11
+    (64, 12, [768], [768], True),                       # 36 items of 24
+    (128, 10, [512] * 4 + [256] * 2, [1408, 1472, 768, 128, 64, 0], False),   # 4 to 31 tiles
+    (64, 10, [256, 512], [0, 2688], True),              # 4 and 50
+])
+def test_attn_split_where_it_ends_sooner(A, hd, heads, q_lens, caches, split):
+    """Few items of few tiles run whole where the tail ranges would be several short
+    pieces.  A dense call writes its workspace only if it splits."""
+    import torch
+    from harness import parity
+    from test_gpu_parity import _attn_case
+    sh = BlockShape(dim=heads * hd, n_heads=heads, head_dim=hd, ffn_dim=512, frames=1, lat_h=8, lat_w=8)
+    pc, dims, batch, q, o, qs, ks, vs = _attn_case(A, sh, q_lens, caches, 424)
+    n = A.ardit_workspace_size(dims, batch)
+    ws = torch.full((n,), 0xA5, dtype=torch.uint8, device="cuda")
+    A.ardit_attn_fwd(None, dims, batch, q, pc.kv(A), o, ws, n)
+    _sync()
+    assert bool((ws != 0xA5).any()) == split
+    got, off = host_f32(o).reshape(-1, heads, hd), 0
+    for b, m in enumerate(q_lens):
+        for h in (0, heads - 1):
+            ref = O.attention(qs[b][:, h:h + 1], ks[b][:, h:h + 1], vs[b][:, h:h + 1])
+            parity(got[off:off + m, h:h + 1], ref, f"stream {b} head {h}", quantum=ref)
+        off += m
+
+
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("lat,frames", [
     ((4, 8), 150),    # 32 keys a frame: a tile is two frames, the page window moves twice

@@ -644,7 +644,8 @@ __device__ __forceinline__ void attn_range(const AttnArgs& a, const AttnStream& 
 
 // One workgroup per item.  At d = 64 past one round two workgroups share a CU (64 KB
 // of LDS each), if a lane takes at most 128 registers: five streams of 3328 queries
-// over 17728 keys, 20 heads, 2190 us with 148, 1760 so.
+// over 17728 keys, 20 heads, 2190 us with 148, 1760 so.  AttnArgs::alone keeps them
+// apart (launch_attn_t).
 template <int HD, bool PAGED, bool VEC>
 __global__ __launch_bounds__(NTHR, HD == 64 ? 4 : 1) void attn_kernel(const AttnArgs a) {
   __shared__ __attribute__((aligned(16))) bf16_t sK[NSLOT * BKV * HD];
@@ -1052,8 +1053,8 @@ int64_t runs_cost(const CostRuns& c, int i0, int i1) {
 
 // Contiguous split of the items over the XCDs that minimises the makespan of
 // the slowest XCD under list scheduling (binary search on the makespan), with
-// the items spread evenly by cost where that makespan allows.
-void split_by_makespan(const CostRuns& c, int n, int64_t total, int32_t* begin) {
+// the items spread evenly by cost where that makespan allows.  Returns the makespan.
+int64_t split_by_makespan(const CostRuns& c, int n, int64_t total, int32_t* begin) {
   int64_t lo = 0, hi = total;
   for (int r = 0; r < c.n; ++r)
     if (c.begin[r + 1] > c.begin[r]) lo = c.cost[r] > lo ? c.cost[r] : lo;
@@ -1083,8 +1084,9 @@ void split_by_makespan(const CostRuns& c, int n, int64_t total, int32_t* begin) 
       i = e;
       begin[x + 1] = i;
     }
-    if (i == n) return;
+    if (i == n) return lo;
   }
+  return lo;
 }
 
 // The last plans' XCD splits, reused while the item costs repeat (every layer
@@ -1099,6 +1101,7 @@ struct XcdSplitCache {
     int32_t key[2 * kMaxStreams + 1];
     int key_len = -1;
     int32_t begin[kNumXcd + 1];
+    int32_t alone;
   } e[kXcdSplitEntries];
   int next = 0;   // the entry replaced next
 };
@@ -1124,6 +1127,8 @@ void balance_items_over_xcds(AttnArgs& a, bool sparse) {
   }
   const int n = a.total_items;
   runs.begin[a.n_streams] = n;
+  int64_t longest = 0;
+  for (int i = 0; i < a.n_streams; ++i) longest = runs.cost[i] > longest ? runs.cost[i] : longest;
   const XcdSplitCache::Entry* hit = nullptr;
   for (const XcdSplitCache::Entry& c : cache.e)
     if (c.key_len == key_len && memcmp(key, c.key, sizeof(int32_t) * static_cast<size_t>(key_len)) == 0) {
@@ -1133,8 +1138,16 @@ void balance_items_over_xcds(AttnArgs& a, bool sparse) {
   if (!hit) {
     XcdSplitCache::Entry& c = cache.e[cache.next];
     cache.next = (cache.next + 1) % kXcdSplitEntries;
+    c.alone = 0;
     if (n <= 65536) {
-      split_by_makespan(runs, n, total, c.begin);
+      const int64_t end = split_by_makespan(runs, n, total, c.begin);
+      // Two workgroups of a CU run at about 0.6 of the speed of one each.  That
+      // delays the end where the longest items take the whole time by themselves, all
+      // others fit beside them and little room is left.  us together and apart, d = 64,
+      // 4672 queries, 8 heads: streams of 512 and 220 tiles 712 / 658; of 512 and 80
+      // (a third of the room left) 660 / 657; of 512 and 440 (two rounds) 981 / 1129;
+      // 10 heads, 192 and 73 265 / 346.
+      c.alone = 32 * end <= 33 * longest && 10 * kNumXcd * kCusPerXcd * end <= 13 * total;
     } else {   // very large batches: equal item counts
       for (int x = 0; x <= kNumXcd; ++x)
         c.begin[x] = static_cast<int32_t>(static_cast<int64_t>(n) * x / kNumXcd);
@@ -1144,6 +1157,7 @@ void balance_items_over_xcds(AttnArgs& a, bool sparse) {
     hit = &c;
   }
   int most = 0;
+  a.alone = hit->alone;
   for (int x = 0; x <= kNumXcd; ++x) a.xcd_begin[x] = hit->begin[x];
   for (int x = 0; x < kNumXcd; ++x)
     most = a.xcd_begin[x + 1] - a.xcd_begin[x] > most ? a.xcd_begin[x + 1] - a.xcd_begin[x] : most;
@@ -1158,8 +1172,8 @@ namespace {
 
 // When a split schedule ends, in 64ths of a tile after the time of a whole item
 // without its tiles.  A range's pieces after the first cost a start and a partial
-// store each (7.9 us at d = 128, 2.6 at d = 64), every schedule the merge's launch,
-// and every partial tile its trip to memory and back.  Fitted to 222 calls of one
+// store each (5 tiles, about 7 us, at d = 128; 2, 2.6 us, at d = 64), every schedule the
+// merge's launch, and every partial tile its trip to memory and back.  Fitted to 222 calls of one
 // round or less (8 to 200 items of 11 to 120 tiles), each timed whole and split;
 // the rule takes the slower side by at most 5% in any of them.  Before it every
 // round cut below 256 workgroups was split, and the short tails of items of 11 to 15
@@ -1223,6 +1237,7 @@ void plan_attention(AttnArgs& a, int head_dim, float* split_ws) {
   a.n_streams = n;
   a.total_items = items;
   a.small = 0;
+  a.alone = 0;
   a.item0 = 0;
   a.total_tiles = 0;
   a.split_blocks = 0;
@@ -1327,6 +1342,7 @@ void plan_attention(AttnArgs& a, int head_dim, float* split_ws) {
   if (!a.split_blocks) balance_items_over_xcds(a, false);
 }
 
+constexpr size_t kAloneLds = 20 * 1024;   // 64 + 20 KB: one workgroup in a CU's 160 KB
 template <int HD, bool P, bool V>
 static void launch_attn_t(hipStream_t st, const AttnArgs& a, dim3 grid) {
   if (a.small) {
@@ -1338,7 +1354,9 @@ static void launch_attn_t(hipStream_t st, const AttnArgs& a, dim3 grid) {
     hipLaunchKernelGGL((attn_merge_kernel<HD>),
                        dim3((a.total_items - a.item0) * (BQ / (256 / (HD / 4)))), dim3(256), 0, st, a);
   } else {
-    hipLaunchKernelGGL((attn_kernel<HD, P, V>), grid, dim3(NTHR), 0, st, a);
+    // (unused LDS that leaves no room for a second workgroup)
+    const size_t lds = HD == 64 && a.alone ? kAloneLds : 0;
+    hipLaunchKernelGGL((attn_kernel<HD, P, V>), grid, dim3(NTHR), lds, st, a);
   }
 }
 

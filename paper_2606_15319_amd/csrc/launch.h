@@ -81,6 +81,7 @@ struct AttnArgs {
   int32_t xcd_begin[kNumXcd + 1];  // one workgroup per item: XCD x runs items
                                    // [xcd_begin[x], xcd_begin[x + 1]), in order
   int32_t small;         // items of 32 queries, the keys split between a workgroup's waves
+  int32_t alone;         // d = 64, one workgroup per item: one workgroup to a CU
   int32_t split_blocks;  // 0: one workgroup per item; else the workgroups of a split schedule
   int32_t item0;         // split: items before item0 run whole, in full rounds
   int32_t total_tiles;   // split: tail tiles of all items, concatenated

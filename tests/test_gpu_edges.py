@@ -167,6 +167,24 @@ def test_attn_split_where_it_ends_sooner(A, hd, heads, q_lens, caches, split):
         off += m
 
 
+def test_attn_items_apart(A):
+    """d = 64, 280 items of 48, 30 and 18 tiles: the longest take the whole time and the
+    others fit beside them, so the launch keeps two workgroups from sharing a CU."""
+    from harness import parity
+    from test_gpu_parity import _attn, _attn_case
+    sh = BlockShape(dim=2560, n_heads=40, head_dim=64, ffn_dim=512, frames=1, lat_h=8, lat_w=8)
+    q_lens, caches = [640, 512, 512], [2432, 1408, 640]
+    pc, dims, batch, q, o, qs, ks, vs = _attn_case(A, sh, q_lens, caches, 426)
+    _attn(A, dims, batch, q, pc.kv(A), o)
+    _sync()
+    got, off = host_f32(o).reshape(-1, 40, 64), 0
+    for b, m in enumerate(q_lens):
+        for h in (0, 17, 39):
+            ref = O.attention(qs[b][:, h:h + 1], ks[b][:, h:h + 1], vs[b][:, h:h + 1])
+            parity(got[off:off + m, h:h + 1], ref, f"stream {b} head {h}", quantum=ref)
+        off += m
+
+
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("lat,frames", [
     ((4, 8), 150),    # 32 keys a frame: a tile is two frames, the page window moves twice

@@ -24,9 +24,9 @@
 // consume them.
 //
 // When the items are so few that one workgroup per item would leave more than
-// a quarter of the CUs idle, each item keeps the first part of its key range
-// and the idle workgroups share the remaining parts; the pieces leave partial
-// results (unnormalised O, running max and denominator in fp32) that a second
+// a quarter of the CUs idle, and it ends sooner, each item keeps the first part of
+// its key range and the idle workgroups share the remaining parts; the pieces leave
+// partial results (unnormalised O, running max and denominator in fp32) that a second
 // kernel merges.  A last round of items that leaves as many idle is cut the same
 // way after the full rounds (plan_attention).  Calls of few queries over few keys
 // take workgroups of 32 queries that split the keys between their waves
@@ -160,8 +160,9 @@ __device__ __forceinline__ void store_partial(const AttnArgs& a, size_t slot,
 //
 // What bounds it: the matrix pipe (64 MFMAs of 16 clocks a wave and tile), the
 // issue port that MFMAs (8 clocks each) and vector instructions (4; exponentials
-// 8) share, at a clock that the card lowers under the load (2.17 GHz of 2.4 over
-// 32760 keys of 12 heads, 1.95 over 37440 of 40).  Two waves share a SIMD, w and
+// 8) share, at a clock that the card lowers under the load (2.15 GHz of 2.4 over
+// 32760 keys of 12 heads, 1.95 over 37440 of 40, with the matrix cores busy 54 and
+// 60% of it: a large product keeps them 91% busy at 1.72).  Two waves share a SIMD, w and
 // w + 4.  When all eight met at a barrier every tile they ran in step: both in
 // the products, then both in the softmax, about 4000 clocks a tile where the
 // products take 2048.  So the two halves of the workgroup are a half tile
@@ -1286,10 +1287,9 @@ void plan_attention(AttnArgs& a, int head_dim, float* split_ws) {
   // items) 78 tiles 125 / 191, 220 330 / 396, 512 765 / 817; 56 idle 78 120 / 151,
   // 220 320 / 332, 313 455 / 450, 512 739 / 709; 64 idle 78 120 / 129, 128 188 /
   // 191, 220 316 / 304, 512 732 / 668.  (So from about a quarter idle on it depends
-  // on the tiles too, which the rule does not weigh.)  The round is cut to as many
-  // workgroups as have eight tiles each (a multiple of the XCDs; 1440 queries over
-  // 4320 keys, 4 heads of 64, 1632 tiles on 24 items: 92 us unsplit, 34 on 200
-  // workgroups), and split only where that ends sooner (split_end).
+  // on the tiles too: split_end.)  The round is cut to as many workgroups as have
+  // eight tiles each (a multiple of the XCDs; 1440 queries over 4320 keys, 4 heads
+  // of 64, 1632 tiles on 24 items: 92 us unsplit, 34 on 200 workgroups).
   //
   // Items of equal cost that fill one to three rounds and leave more than a
   // quarter of the last one idle run their full rounds whole and split the rest

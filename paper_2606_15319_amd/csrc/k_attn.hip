@@ -1171,12 +1171,12 @@ size_t attention_split_bytes(int head_dim) {
 
 namespace {
 
-// When a split schedule ends, in 64ths of a tile after the time of a whole item
+// When a split schedule ends, in 128ths of a tile after the time of a whole item
 // without its tiles.  A range's pieces after the first cost a start and a partial
-// store each (5 tiles, about 7 us, at d = 128; 2, 2.6 us, at d = 64), every schedule the
-// merge's launch, and every partial tile its trip to memory and back.  Fitted to 222 calls of one
-// round or less (8 to 200 items of 11 to 120 tiles), each timed whole and split;
-// the rule takes the slower side by at most 5% in any of them.  Before it every
+// store each (5 tiles, about 7 us, at d = 128; 2.5, 3 us, at d = 64), every schedule the
+// merge's launch, and every partial tile its trip to memory and back.  Fitted to 464
+// calls of one round or less (8 to 200 items of 11 to 120 tiles), each timed whole and
+// split; the rule takes the slower side by at most 5% in any of them.  Before it every
 // round cut below 256 workgroups was split, and the short tails of items of 11 to 15
 // tiles put two and three pieces into a range: us whole and split, d = 128: 36 items
 // of 14 tiles 28.8 / 43.6, 176 of 11 27.9 / 49.5, streams of 4 to 31 tiles, 100
@@ -1203,8 +1203,8 @@ int64_t split_end(const AttnStream* s, int n, int split_tiles, int64_t tails, in
   int most = 0;
   for (int r = 0; r < kAttnSplitBlocks; ++r) most = max(most, pieces[r]);
   const bool wide = head_dim == 128;
-  const int64_t last = S + (wide ? 5 : 2) * (most - 1);
-  return 64 * max(static_cast<int64_t>(longest), last) + (wide ? 320 + parts : 128 + 2 * parts);
+  const int64_t last = 128 * S + (wide ? 640 : 320) * (most - 1);
+  return max(static_cast<int64_t>(128) * longest, last) + (wide ? 640 + 2 * parts : 384 + 3 * parts);
 }
 
 }  // namespace
@@ -1324,7 +1324,7 @@ void plan_attention(AttnArgs& a, int head_dim, float* split_ws) {
     }
     const int split_tiles = static_cast<int>((tails + spare - 1) / spare);
     if (tails > 0 &&
-        split_end(tmp, n, split_tiles, tails, head_dim) < 64 * static_cast<int64_t>(tmp[0].n_tiles)) {
+        split_end(tmp, n, split_tiles, tails, head_dim) < 128 * static_cast<int64_t>(tmp[0].n_tiles)) {
       a.item0 = item0;
       a.split_blocks = blocks;
       a.total_tiles = static_cast<int32_t>(tails);

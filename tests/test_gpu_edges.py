@@ -199,7 +199,7 @@ def test_attn_page_walk(A, hd, lat, frames):
     from test_gpu_parity import _attn, _attn_case
     T = lat[0] * lat[1]
     sh = BlockShape(dim=8 * hd, n_heads=8, head_dim=hd, ffn_dim=512, frames=1, lat_h=lat[0], lat_w=lat[1])
-    q_len = 1025 if frames < 100 else 300   # (over 256 workgroups of 32 queries, or over 64 tiles)
+    q_len = 1025 if frames < 100 else 300   # (over 256 workgroups of 32 queries, or over 47 tiles)
     pc, dims, batch, q, o, qs, ks, vs = _attn_case(A, sh, [q_len], [T * frames], 423)
     _attn(A, dims, batch, q, pc.kv(A), o)
     _sync()
